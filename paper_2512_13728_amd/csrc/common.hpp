@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "i8_digits.hpp"
 #include "plan.hpp"
 
 namespace cd {
@@ -162,7 +163,6 @@ inline bool gemm_acc64(GemmKind k) { return k != GemmKind::F32; }
 // when a_kc, else A[k*lda + i]) and B K x N row-major, fp32 or fp64, cut into
 // digit planes by launch_slice8 first.  K is split in `splits` slices of
 // kchunk (a multiple of 64, at most I8_KMAX: the int32 sums stay exact).
-constexpr int I8_KMAX = 16384;
 constexpr int I8_RMIN = 33;        // narrower products stay on the fp64 MFMA kernel
 // Gram matrices take it from this rank on (one 64 x 64 tile and less: the fp64
 // kernel, 18 us at 4096 x 64), and up to this many layers in flight over the

@@ -13,7 +13,7 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import oracle as O  # noqa: E402
 import paper_2512_13728_amd as cdl  # noqa: E402
 import synthetic as S  # noqa: E402
-from gpu_util import check_errors, step_and_compare  # noqa: E402
+from gpu_util import check_errors, group_step_and_compare, step_and_compare  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -106,3 +106,28 @@ def test_update_pieces(m, n, r):
     print(f"{m}x{n} r={r}", {k: v for k, v in d.items() if k.startswith("err") or k == "kappa"}, flush=True)
     for k in ("err_M", "err_X", "err_dM", "err_dX"):
         assert d[k] < 1e-5, (k, d[k])
+
+
+def _dominant(m, n, r, f, seed):
+    """G, M, X, Q of a layer whose buffer has one row f times the others."""
+    g = torch.Generator().manual_seed(seed)
+    randn = lambda *s: torch.randn(s, generator=g)  # noqa: E731
+    G = 4 * randn(m, 48) @ randn(48, n) + 0.4 * randn(m, n)
+    G[7] *= f
+    Q = torch.linalg.qr(randn(n, r).double())[0].float()
+    return tuple(t.cuda().contiguous() for t in (G, torch.zeros(m, n), 0.02 * randn(m, n), Q))
+
+
+# the Gram matrix's smallest pivots are 9 to 80 times the floor of 1e-13 of its
+# largest diagonal entry (kappa(P~) up to 4e6), in K slices of 256 rows (one
+# layer) and of all 2048 (13 layers fill the chip)
+@pytest.mark.parametrize("m,n,r,layers,f", [(2048, 512, 256, 1, 1e5), (1024, 1024, 96, 1, 2e5), (2048, 768, 512, 13, 6e4)])
+def test_gram_dominant_row(m, n, r, layers, f):
+    Ls = [cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC) for _ in range(layers)]
+    G, M, X, Q = (list(t) for t in zip(*[_dominant(m, n, r, f, 790 + i) for i in range(layers)]))
+    grp = cdl.Group(Ls)
+    _, errs = group_step_and_compare(grp, Ls, G, M, X, Q, 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC, check=[0])
+    d = errs[0]
+    print(f"{m}x{n} r={r} x{layers}", {k: v for k, v in d.items() if k.startswith("err") or k in ("kappa", "orth_P")}, flush=True)
+    assert not any(L.rank_deficient() for L in Ls)
+    assert d["err_P"] < 1e-5 and d["err_Q"] < 1e-5 and d["orth_P"] < 1e-5, d
