@@ -84,8 +84,8 @@ POLICIES = {"rmmc": 0, "always": 1, "never": 2, "every_h": 3}
 # kernel kind -> (kernel-name pattern in the profiler's output, source files);
 # kinds whose kernel template is shared with other kinds have no pattern
 CSRC = os.path.join(ROOT, "paper_2512_13728_amd", "csrc")
-_STREAM = ["k_stream.hip", "common.hpp", "plan.hpp"]
-_BF = ["k_gemm_bf.hip", "bf16_split.hpp", "mfma_tile.hpp", "common.hpp", "plan.hpp"]
+_STREAM = ["k_stream.hip", "common.hpp", "i8_digits.hpp", "plan.hpp"]
+_BF = ["k_gemm_bf.hip", "bf16_split.hpp", "mfma_tile.hpp", "common.hpp", "i8_digits.hpp", "plan.hpp"]
 KIND_KERNEL = {
     "form_buffer": (r"k_form_buffer<\w+, 0>", _STREAM),
     "form_buffer_local": (r"k_form_buffer<\w+, 1>", _STREAM),
@@ -93,8 +93,8 @@ KIND_KERNEL = {
     "gate": (r"k_gate\b", _STREAM),
     "update_bf16": (r"k_update_pl<1,", _BF),
     "update_bf16x6": (r"k_update_pl<3,", _BF),
-    "update_f32": (r"k_update_vec<", ["k_update_vec.hip", "common.hpp", "plan.hpp"]),
-    "cholesky_f64": (None, ["k_chol.hip", "chol_block.hpp", "mfma_tile.hpp", "common.hpp", "plan.hpp"]),
+    "update_f32": (r"k_update_vec<", ["k_update_vec.hip", "common.hpp", "i8_digits.hpp", "plan.hpp"]),
+    "cholesky_f64": (None, ["k_chol.hip", "chol_block.hpp", "mfma_tile.hpp", "common.hpp", "i8_digits.hpp", "plan.hpp"]),
 }
 COPY_PATTERN = r"neg_kernel"          # the calibration copy: b = -a, fp32, elementwise
 PMC_PROFILE = os.path.join(ROOT, "profiles", "{workload}_hbm_traffic_pmc.txt")
