@@ -64,7 +64,7 @@ KIND_BOUND = {
     "power_btp_f64": ("mfma", "f64", 1),
     # fp64-accurate products from 21 digit products on the int8 MFMA
     "power_bq_i8x21": ("mfma", "i8", 21), "power_btp_i8x21": ("mfma", "i8", 21), "slice_i8": ("hbm", None, 1),
-    "gram_i8x21": ("mfma", "i8", 21),
+    "gram_i8x26": ("mfma", "i8", 26), "range_i8": ("hbm", None, 1),
     "cholesky_f64": ("mfma", "f64", 1), "power_bq_bf16x6": ("mfma", "bf16", 6),
     "update_bf16x6": ("mfma", "bf16", 6),
     "update_f16x3": ("mfma", "bf16", 3),   # fp16 pieces: the bf16 rate

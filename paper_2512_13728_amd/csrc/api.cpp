@@ -119,13 +119,15 @@ bool plan_i8(int M, int N, int K, int nl, int conc, int* splits, int* kchunk) {
 // ---- optional per-kernel timing (HIP events on the launch stream) ----------
 enum Kind { K_FORM, K_FORM_X, K_GATE, K_LOCAL, K_PBQ, K_PBQ_BF, K_GRAM, K_GRAM_BF, K_CHOL, K_APPLY_F64,
             K_APPLY_BF, K_PBTP, K_PBTP3, K_REDUCE, K_COLNORM, K_UPDATE, K_UPDATE_BF1, K_UPDATE_F32,
-            K_SMALL_QR, K_SMALL_UPD, K_GRAM_X, K_FORM_BQ, K_SLICE8, K_PBQ_I8, K_PBTP_I8, K_UPDATE_F16, K_GRAM_I8, K_NKINDS };
+            K_SMALL_QR, K_SMALL_UPD, K_GRAM_X, K_FORM_BQ, K_SLICE8, K_PBQ_I8, K_PBTP_I8, K_UPDATE_F16, K_GRAM_I8,
+            K_RANGE8, K_NKINDS };
 const char* const kKindName[K_NKINDS] = {
     "form_buffer", "form_buffer_local", "gate", "local_update", "power_bq_f64", "power_bq_bf16x3", "gram_f64",
     "gram_bf16x6", "cholesky_f64", "apply_f64", "apply_bf16x6", "power_btp_f64",
     "power_btp_bf16x3", "reduce_splits", "colnorm", "update_bf16x6", "update_bf16", "update_f32",
     "small_cholqr", "small_update", "gram_bf16x9", "form_power_bq_bf16x3",
-    "slice_i8", "power_bq_i8x21", "power_btp_i8x21", "update_f16x3", "gram_i8x21"};
+    "slice_i8", "power_bq_i8x21", "power_btp_i8x21", "update_f16x3", "gram_i8x26",
+    "range_i8"};
 static_assert(K_NKINDS <= 32, "the timing mask holds one bit per kind");
 
 // Timing events only measure: recording them without the system-scope fence
@@ -208,17 +210,11 @@ struct cd_layer {
   // Products on the int8 MFMA (fp32-gradient layers).  The digit planes of Q
   // lie over P1 and the update's planes (neither is written before P~ is
   // complete), those of P over the same (P1 is dead, the planes come after
-  // R).  The buffer pass leaves its largest |B| per block in pa, P~'s place,
-  // and the gate the layer's beside the pivot floor.
+  // R).  B's row maxima lie in P's place and the partial column maxima in R's
+  // (both are written later in the step), the column maxima in colsq's
+  // (4 n bytes of at least 4.1 n; their last use is R).
   char* digits() const { return reinterpret_cast<char*>(pb); }
-  float* amax() const { return reinterpret_cast<float*>(floor_ + 1); }
-  float* pmax() const {
-    const long long mn = 1LL * d.m * d.n;
-    if (d.grad_dtype != CD_F32 || d.r_max < cd::I8_RMIN ||
-        (mn + cd::FORM_CHUNK - 1) / cd::FORM_CHUNK * 4 > 8LL * d.m * d.r_max)
-      return nullptr;
-    return reinterpret_cast<float*>(pa);
-  }
+  float* cmax() const { return reinterpret_cast<float*>(colsq); }
 };
 
 struct ShapeClass {
@@ -254,8 +250,6 @@ struct cd_group {
   std::vector<int> np_fx;       // the same on the host; empty: no fused pass planned
   double** prev = nullptr;      // [L] device pointers to each layer's prev_norm
   double* norms = nullptr;      // [L] gate workspace
-  cd::GateTab* gtab = nullptr;  // [L] where the largest |B| goes (fp32 gradients)
-  bool wants_max = false;       // some layer's products may need it
   unsigned* counter = nullptr;  // gate completion counter (returns to zero)
   cd::StepCtl* ctl = nullptr;   // the step's decision on the device (see cd::StepCtl)
   // RMMC policy: the branch predicted for the next step, when the host knows
@@ -434,7 +428,7 @@ GroupLayout group_layout(int L, int nparts_stride) {
   lo.nparts = c.put(sizeof(int) * L);
   lo.nparts_fx = c.put(sizeof(int) * L);
   lo.prev = c.put(sizeof(double*) * L);
-  lo.norms = c.put((sizeof(double) + sizeof(cd::GateTab)) * L);   // and gtab
+  lo.norms = c.put(sizeof(double) * L);
   lo.counter = c.put(sizeof(unsigned));
   lo.ctl = c.put(sizeof(cd::StepCtl));
   lo.out_dev = c.put(sizeof(cd::GateOut) + sizeof(double) * L);
@@ -449,7 +443,6 @@ void carve_group(cd_group* g, char* base, const GroupLayout& lo) {
   g->nparts_fx = reinterpret_cast<int*>(base + lo.nparts_fx);
   g->prev = reinterpret_cast<double**>(base + lo.prev);
   g->norms = reinterpret_cast<double*>(base + lo.norms);
-  g->gtab = reinterpret_cast<cd::GateTab*>(g->norms + g->L);
   g->counter = reinterpret_cast<unsigned*>(base + lo.counter);
   g->ctl = reinterpret_cast<cd::StepCtl*>(base + lo.ctl);
   g->out_dev = reinterpret_cast<cd::GateOut*>(base + lo.out_dev);
@@ -470,7 +463,7 @@ cd::CholTab factor_tab(const cd_layer* L, int* rankdef_host) {
 // launches; the table's contents go to ct.
 // rankdef_host: the device view of the group's L-int rank-deficiency mirror.
 void plan_group(cd_group* g, cd_layer* const* layers, int n, std::vector<int>& np, std::vector<double*>& pv,
-                std::vector<cd::CholTab>& ct, std::vector<cd::GateTab>& gt, int* rankdef_host) {
+                std::vector<cd::CholTab>& ct, int* rankdef_host) {
   g->layers.assign(layers, layers + n);
   g->L = n;
   g->device = layers[0]->device;
@@ -495,12 +488,9 @@ void plan_group(cd_group* g, cd_layer* const* layers, int n, std::vector<int>& n
   np.assign(n, 0);
   pv.assign(n, nullptr);
   ct.assign(n, cd::CholTab{});
-  gt.assign(n, cd::GateTab{});
   for (int i = 0; i < n; ++i) {
     np[i] = static_cast<int>(blocks_for(1LL * layers[i]->d.m * layers[i]->d.n));
     pv[i] = layers[i]->prev;
-    gt[i] = cd::GateTab{layers[i]->pmax(), layers[i]->amax()};
-    g->wants_max = g->wants_max || gt[i].pmax != nullptr;
   }
   int off = 0;
   for (int c = 0; c < static_cast<int>(g->shapes.size()); ++c) {
@@ -548,7 +538,6 @@ cd_status build_group(cd_layer* const* layers, int n, cd_group** out) {
   std::vector<int> np;
   std::vector<double*> pv;
   std::vector<cd::CholTab> ct;
-  std::vector<cd::GateTab> gt;
   g->device = layers[0]->device;
   DeviceGuard dg(g->device);
   if (!dg.ok) { free_group(g); return fail(CD_EHIP, "cannot select device %d", g->device); }
@@ -559,7 +548,7 @@ cd_status build_group(cd_layer* const* layers, int n, cd_group** out) {
     free_group(g);
     return fail(e == hipErrorOutOfMemory ? CD_ENOMEM : CD_EHIP, "group setup: %s", hipGetErrorString(e));
   }
-  plan_group(g, layers, n, np, pv, ct, gt,
+  plan_group(g, layers, n, np, pv, ct,
              reinterpret_cast<int*>(static_cast<char*>(g->out_host_dev) + host_rankdef_off(n)));
   const GroupLayout lo = group_layout(n, g->nparts_stride);
   e = hipMalloc(&g->tables, lo.total);
@@ -574,7 +563,6 @@ cd_status build_group(cd_layer* const* layers, int n, cd_group** out) {
   if (e == hipSuccess && !g->np_fx.empty())
     e = hipMemcpy(g->nparts_fx, g->np_fx.data(), sizeof(int) * n, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(g->prev, pv.data(), sizeof(double*) * n, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g->gtab, gt.data(), sizeof(cd::GateTab) * n, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(g->chol_tab, ct.data(), sizeof(cd::CholTab) * n, hipMemcpyHostToDevice);
   if (g->units.size() > 1) {
     g->nside = std::min(static_cast<int>(g->units.size()) - 1, cd_group::NSIDE);
@@ -742,7 +730,7 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
       ia.C[j] = ia.splits > 1 ? lay(j)->gram_part : lay(j)->W;
     }
     const double mrd = 1.0 * m * r;
-    cd_status st2 = run(g, K_SLICE8, 14.0 * mrd * nl, 0.0, s, [&] { return cd::launch_slice8(ia, nl, s); });
+    cd_status st2 = run(g, K_SLICE8, 14.0 * mrd * nl, 0.0, s, [&] { return cd::launch_slice8(ia, nullptr, nl, s); });
     if (st2 != CD_OK) return st2;
     st2 = run(g, K_GRAM_I8, (6.0 * mrd + 8.0 * r * r) * nl, mrd * (r + 1) * nl, s,
               [&] { return cd::launch_gemm_i8(ia, nl, s); });
@@ -753,28 +741,46 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
     return run(g, K_REDUCE, static_cast<double>(ra.count) * nl * 8.0 * (ia.splits + 1), 0.0, s,
                [&] { return cd::launch_reduce_splits(ra, nl, true, true, s); });
   };
-  // The same product of an fp32-gradient layer on the int8 MFMA, to fp64
-  // accuracy: the digit planes of the small operand (K x r, fp32 or fp64),
-  // the product and the sum of its K slices.  done = false: the product stays
-  // on the fp64 MFMA (ranks below I8_RMIN, where that kernel's narrow tiles
-  // pad less and streaming B bounds both; slices too long for int32 sums;
-  // planes or maxima that the workspace has no room for).
-  auto gemm_i8 = [&](int tkind, int Mr, int K, bool a_kc, bool b64, bool out64, double bytes, auto Aof, auto Bof,
-                     auto Cof, bool* done) -> cd_status {
+  // The power products of fp32-gradient layers on the int8 MFMA: P~ = B Q
+  // (`first`; before it B's row and column maxima, the scales of both), then
+  // R = B^T P; each the digit planes of the small operand (K x r, fp32 or
+  // fp64), the product and the sum of its K slices.  done = false: they stay on
+  // the fp64 MFMA (ranks below I8_RMIN, where that kernel's narrow tiles pad
+  // less and streaming B bounds both; slices too long for int32 sums; planes or
+  // maxima that the workspace has no room for, in either product).
+  auto gemm_i8 = [&](bool first, auto Aof, auto Bof, auto Cof, bool* done) -> cd_status {
     *done = false;
     cd::I8Args ia{};
-    if (r < cd::I8_RMIN || !plan_i8(Mr, r, K, nl, conc, &ia.splits, &ia.kchunk)) return CD_OK;
-    const size_t need = cd::i8_bytes(r, ia.splits, ia.kchunk);
-    for (int j = 0; j < nl; ++j)
-      if (!lay(j)->pmax() || need > lay(j)->digit_cap ||
-          (ia.splits > 1 && sizeof(double) * ia.splits * Mr * r > lay(j)->split_cap))
-        return CD_OK;
+    cd::RangeArgs ra8{};
+    if (r < cd::I8_RMIN || !cd::plan_range(m, n, r, &ra8.tr, &ra8.tc)) return CD_OK;
+    for (const bool other : {true, false}) {   // the other product's plan, then this one's
+      const int Mp = first != other ? m : n, Kp = first != other ? n : m;
+      if (!plan_i8(Mp, r, Kp, nl, conc, &ia.splits, &ia.kchunk)) return CD_OK;
+      const size_t need = cd::i8_bytes(r, ia.splits, ia.kchunk);
+      for (int j = 0; j < nl; ++j)
+        if (need > lay(j)->digit_cap || (ia.splits > 1 && sizeof(double) * ia.splits * Mp * r > lay(j)->split_cap))
+          return CD_OK;
+    }
     *done = true;
+    const int Mr = first ? m : n, K = first ? n : m;
+    const double mnd = 1.0 * m * n, kr = 1.0 * K * r;
+    cd_status st2 = CD_OK;
+    if (first) {
+      ra8.m = m; ra8.n = n; ra8.run_if = run_if;
+      for (int j = 0; j < nl; ++j) {
+        ra8.B[j] = static_cast<const float*>(Aof(j));
+        ra8.rows[j] = lay(j)->P;
+        ra8.cols[j] = lay(j)->R;
+        ra8.cmax[j] = lay(j)->cmax();
+      }
+      st2 = run(g, K_RANGE8, 4.0 * mnd * nl, 0.0, s, [&] { return cd::launch_range8(ra8, nl, s); });
+      if (st2 != CD_OK) return st2;
+    }
     ia.M = Mr; ia.N = r; ia.K = K; ia.lda = n;
     ia.np = (r + 31) / 32 * 32;
     ia.kblocks = ia.splits * ia.kchunk / 32;
     ia.split_stride = 1LL * Mr * r;
-    ia.a_kc = a_kc; ia.b64 = b64; ia.out64 = out64; ia.run_if = run_if;
+    ia.a_kc = first; ia.b64 = !first; ia.out64 = first; ia.run_if = run_if;
     const size_t planes = cd::i8_plane_bytes(r, ia.splits, ia.kchunk);
     for (int j = 0; j < nl; ++j) {
       ia.A[j] = Aof(j);
@@ -782,20 +788,20 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
       ia.Bpl[j] = lay(j)->digits();
       ia.Bsc[j] = reinterpret_cast<double*>(lay(j)->digits() + planes);
       ia.Bmx[j] = ia.Bsc[j] + 1LL * ia.splits * ia.np;
-      ia.amax[j] = lay(j)->amax();
+      ia.Amx[j] = first ? lay(j)->P : lay(j)->cmax();
       ia.C[j] = ia.splits > 1 ? lay(j)->split_part : Cof(j);
     }
-    const double kr = 1.0 * K * r;
-    cd_status st2 = run(g, K_SLICE8, (6.0 + (b64 ? 8.0 : 4.0)) * kr * nl, 0.0, s,
-                        [&] { return cd::launch_slice8(ia, nl, s); });
+    st2 = run(g, K_SLICE8, (6.0 + (first ? 4.0 : 8.0)) * kr * nl, 0.0, s,
+              [&] { return cd::launch_slice8(ia, first ? &ra8 : nullptr, nl, s); });
     if (st2 != CD_OK) return st2;
-    st2 = run(g, tkind, bytes * nl, 2.0 * m * n * r * nl, s, [&] { return cd::launch_gemm_i8(ia, nl, s); });
+    st2 = run(g, first ? K_PBQ_I8 : K_PBTP_I8, (4.0 * mnd + 6.0 * kr + (first ? 8.0 : 4.0) * Mr * r) * nl, 2.0 * mnd * r * nl,
+              s, [&] { return cd::launch_gemm_i8(ia, nl, s); });
     if (st2 != CD_OK || ia.splits == 1) return st2;
     cd::ReduceArgs ra{};
     ra.count = 1LL * Mr * r; ra.stride = ia.split_stride; ra.splits = ia.splits; ra.run_if = run_if;
     for (int j = 0; j < nl; ++j) { ra.part[j] = lay(j)->split_part; ra.out[j] = Cof(j); }
     return run(g, K_REDUCE, static_cast<double>(ra.count) * nl * 8.0 * (ia.splits + 1), 0.0, s,
-               [&] { return cd::launch_reduce_splits(ra, nl, true, out64, s); });
+               [&] { return cd::launch_reduce_splits(ra, nl, true, first, s); });
   };
   const double mn = 1.0 * m * n, mr = 1.0 * m * r, nr = 1.0 * n * r, rr = 1.0 * r * r;
   // eta_local of each layer: what a speculative skip update subtracted
@@ -868,7 +874,7 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
     auto Qf = [&](int j) { return static_cast<const void*>(Q[sel[j]]); };
     auto Pt = [&](int j) { return static_cast<void*>(lay(j)->pa); };
     bool done = false;
-    const cd_status st = gemm_i8(K_PBQ_I8, m, n, true, false, true, 4.0 * mn + 6.0 * nr + 8.0 * mr, Bf, Qf, Pt, &done);
+    const cd_status st = gemm_i8(true, Bf, Qf, Pt, &done);
     if (st != CD_OK || done) return st;
     return gemm(K_PBQ, 2.0 * mn * r, 4.0 * mn + 4.0 * nr + 8.0 * mr, cd::GemmKind::F64_FROM_F32, m, r,
                 n, true, n, false, r, false, Bf, Qf, Pt, part);
@@ -963,7 +969,7 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
     st = gemm(K_PBTP3, 2.0 * mn * r, 4.0 * mn + 4.0 * mr + 4.0 * nr, cd::GemmKind::F32, n, r, m, false, n,
               false, r, false, Bf, [&](int j) { return static_cast<const void*>(lay(j)->P); }, Rf, part, 2);
   else
-    st = gemm_i8(K_PBTP_I8, n, m, false, true, false, 4.0 * mn + 6.0 * mr + 4.0 * nr, Bf, P64, Rf, &done);
+    st = gemm_i8(false, Bf, P64, Rf, &done);
   if (st == CD_OK && !fast && !done)
     st = gemm(K_PBTP, 2.0 * mn * r, 4.0 * mn + 8.0 * mr + 4.0 * nr, cd::GemmKind::F32_F64_TO_F32, n, r, m,
               false, n, false, r, false, Bf, P64, Rf, part);
@@ -1095,8 +1101,6 @@ cd_status enqueue_form(cd_group* g, const void* const* G, float* const* M, float
     cd::FormArgs fa{};
     fa.nl = nl;
     fa.ctl = g->ctl;
-    fa.tab = g->wants_max ? g->gtab : nullptr;
-    fa.l0 = batch[0];   // a batch is a run of layers in group order
     long long total = 0, blocks = 0;
     for (int j = 0; j < nl; ++j) {
       const int li = batch[j];
@@ -1198,7 +1202,6 @@ cd_status enqueue_gate(cd_group* g, hipStream_t s, bool to_host, int spec_mode, 
   ga.nparts = fused ? g->nparts_fx : g->nparts;
   ga.prev = g->prev; ga.eps = g->eps; ga.tau = g->tau; ga.out = g->out_dev;
   ga.norms = g->norms; ga.counter = g->counter;
-  ga.tab = g->wants_max ? g->gtab : nullptr;
   ga.ctl = g->ctl; ga.spec_mode = spec_mode; ga.fixed_flag = fixed_flag;
   if (to_host) {
     ga.host_out = static_cast<cd::GateOut*>(g->out_host_dev);
@@ -1472,8 +1475,6 @@ struct StaticSetup {
   unsigned* counter;
   cd::CholTab* ct;
   cd::CholTab ctv;
-  cd::GateTab* gt;
-  cd::GateTab gtv;
 };
 
 __global__ __launch_bounds__(256) void k_static_setup(StaticSetup a) {
@@ -1482,7 +1483,6 @@ __global__ __launch_bounds__(256) void k_static_setup(StaticSetup a) {
     *a.prev_tab = a.prev;
     *a.counter = 0u;   // the gate's completion counter starts at zero
     *a.ct = a.ctv;
-    *a.gt = a.gtv;
   }
 }
 
@@ -1512,7 +1512,6 @@ void plan_static(cd_group* g, cd_layer* L) {
   g->sbatches.resize(1);
   g->sbatches[0].resize(1);
   g->sbatches[0][0] = 0;
-  g->wants_max = L->pmax() != nullptr;
   g->nside = 0;
   g->out_host = nullptr;
   g->out_host_dev = nullptr;
@@ -1576,8 +1575,6 @@ cd_status static_step_impl(const cd_layer_desc* desc, double* prev_norm, long lo
   su.counter = g->counter;
   su.ct = g->chol_tab;
   su.ctv = factor_tab(L, nullptr);
-  su.gt = g->gtab;
-  su.gtv = cd::GateTab{L->pmax(), L->amax()};
   hipLaunchKernelGGL(k_static_setup, dim3(1), dim3(256), 0, s, su);
   CD_HIP(hipGetLastError());
 

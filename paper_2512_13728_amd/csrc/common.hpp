@@ -44,12 +44,6 @@ __device__ __forceinline__ T* global_view(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)(reinterpret_cast<unsigned long long>(p));
 }
 
-// Where the largest finite |B| of an fp32-gradient layer goes.
-struct GateTab {
-  float* pmax;                     // per block of the buffer pass; NULL: not wanted
-  float* amax;                     // of the layer: {largest finite |B|, 1 if ||B|| is not finite}
-};
-
 // ---- a1: B = M + G and per-block sum of B^2 -------------------------------
 // Every block covers FORM_CHUNK consecutive elements of one layer; one launch
 // covers up to MAXS layers of any shapes (the passes are elementwise), layer
@@ -65,10 +59,6 @@ struct FormArgs {
   float coef[MAXS];                // eta_local per layer (with_x only)
   float xdecay[MAXS];              // 1 - eta * weight_decay per layer (with_x only)
   const StepCtl* ctl;              // spec_mode 2: with_x = ctl->spec_next
-  // fp32 gradients: NULL, or the group's table, this launch's first layer at
-  // l0: per block the largest finite |B| goes to tab[l0 + j].pmax if not NULL
-  const GateTab* tab;
-  int l0;
 };
 // spec_mode: 0 = buffer only, 1 = with the skip update, 2 = as ctl->spec_next says
 hipError_t launch_form_buffer(const FormArgs& a, bool g_bf16, int spec_mode, hipStream_t s);
@@ -116,7 +106,6 @@ struct GateArgs {
   StepCtl* ctl;                    // the decision for the kernels that follow
   int spec_mode;                   // as the step's buffer pass (0, 1, or 2 = ctl->spec_next)
   int fixed_flag;                  // -1: flag = g > tau; else the fixed policy's branch
-  const GateTab* tab;              // NULL, or [L]
 };
 hipError_t launch_gate(const GateArgs& a, hipStream_t s);
 
@@ -188,7 +177,7 @@ struct I8Args {
   char* Bpl[MAXB];                 // its planes: [N / 32][kblocks][6][64 lanes][16 bytes]
   double* Bsc[MAXB];               // column scales per slice: [splits][np]
   double* Bmx[MAXB];               // column maxima per chunk: [splits][chunks][np]
-  const float* amax[MAXB];         // {largest finite |A|, 1 if A holds a NaN or an Inf else 0}
+  const float* Amx[MAXB];          // largest |A(i, .)| of every row, Inf where it holds a NaN or an Inf
   void* C[MAXB];                   // result (splits == 1) or fp64 partials
   const int* run_if;
 };
@@ -207,7 +196,19 @@ inline size_t i8_bytes(int N, int splits, int kchunk) {
 // than 128 x 64 would (B's digits are formed once per column tile).
 inline int gemm_i8_bn(int N) { return (N + 31) / 32 % 4 == 0 || N > 512 ? 128 : 64; }
 inline int gemm_i8_bm(int N) { return 8192 / gemm_i8_bn(N); }
-hipError_t launch_slice8(const I8Args& a, int nl, hipStream_t s);
+// The largest |B| of every row and column of B (m x n): launch_range8 leaves
+// partial maxima per tile of tr x tc, which launch_slice8 joins when it is given
+// the same arguments.
+struct RangeArgs {
+  int m, n, tr, tc;
+  const float* B[MAXB];
+  float* rows[MAXB];               // m maxima, then partials [ceil(n / tc)][m]
+  float* cols[MAXB];               // partials [ceil(m / tr)][n]
+  float* cmax[MAXB];               // n maxima
+  const int* run_if;
+};
+hipError_t launch_range8(const RangeArgs& a, int nl, hipStream_t s);
+hipError_t launch_slice8(const I8Args& a, const RangeArgs* range, int nl, hipStream_t s);
 hipError_t launch_gemm_i8(const I8Args& a, int nl, hipStream_t s);
 
 // The same contraction for fp32 operands on the bf16 MFMA with each operand

@@ -50,12 +50,6 @@ __device__ __forceinline__ float load_g1(const void* G, long long i) {
   }
 }
 
-// largest finite |x| so far (fp32 gradients; a NaN fails the comparison)
-template <bool ON>
-__device__ __forceinline__ void upmax(float& mx, float x) {
-  if constexpr (ON) mx = fmaxf(mx, fabsf(x) <= 3.402823466e38f ? fabsf(x) : 0.0f);
-}
-
 __device__ __forceinline__ double sq(float x) { return static_cast<double>(x) * static_cast<double>(x); }
 
 // Sum over the block in a fixed order; the result is valid in thread 0.
@@ -72,20 +66,6 @@ __device__ double block_sum(double v) {
     for (int i = 0; i < NTHREADS / 64; ++i) s += ws[i];
   }
   return s;
-}
-
-// Largest value over the block (none is NaN); valid in thread 0.
-__device__ float block_max(float v) {
-  __shared__ float wm[NTHREADS / 64];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int i = 0; i < NTHREADS / 64; ++i) v = fmaxf(v, wm[i]);
-  }
-  return v;
 }
 
 constexpr int VPT = FORM_CHUNK / (NTHREADS * 4);   // float4 groups per thread (4)
@@ -118,11 +98,9 @@ __global__ __launch_bounds__(NTHREADS) void k_form_buffer(FormArgs a) {
   float* __restrict__ X = a.X[l];
   const float c = a.coef[l];
   const float d = a.xdecay[l];
-  float* const pm = (BF16 || a.tab == nullptr) ? nullptr : a.tab[a.l0 + l].pmax;
   const long long base = static_cast<long long>(lb) * FORM_CHUNK;
   const long long end = min(base + FORM_CHUNK, a.numel[l]);
   double acc = 0.0;
-  float mx = 0.0f;
   if (end - base == FORM_CHUNK) {
     float4 m[VPT], g[VPT], x[VPT];
 #pragma unroll
@@ -140,7 +118,6 @@ __global__ __launch_bounds__(NTHREADS) void k_form_buffer(FormArgs a) {
       b.z = m[v].z + g[v].z; b.w = m[v].w + g[v].w;
       st_nt(M + i, b);
       acc += sq(b.x); acc += sq(b.y); acc += sq(b.z); acc += sq(b.w);
-      upmax<!BF16>(mx, b.x); upmax<!BF16>(mx, b.y); upmax<!BF16>(mx, b.z); upmax<!BF16>(mx, b.w);
       if (wx) {
         float4 y;
         y.x = fmaf(-c, g[v].x, d * x[v].x); y.y = fmaf(-c, g[v].y, d * x[v].y);
@@ -157,7 +134,6 @@ __global__ __launch_bounds__(NTHREADS) void k_form_buffer(FormArgs a) {
         b.x = mv.x + gv.x; b.y = mv.y + gv.y; b.z = mv.z + gv.z; b.w = mv.w + gv.w;
         *reinterpret_cast<float4*>(M + i) = b;
         acc += sq(b.x); acc += sq(b.y); acc += sq(b.z); acc += sq(b.w);
-        upmax<!BF16>(mx, b.x); upmax<!BF16>(mx, b.y); upmax<!BF16>(mx, b.z); upmax<!BF16>(mx, b.w);
         if (wx) {
           const float4 xv = *reinterpret_cast<const float4*>(X + i);
           float4 y;
@@ -171,7 +147,6 @@ __global__ __launch_bounds__(NTHREADS) void k_form_buffer(FormArgs a) {
           const float b = M[j] + gj;
           M[j] = b;
           acc += sq(b);
-          upmax<!BF16>(mx, b);
           if (wx) X[j] = fmaf(-c, gj, d * X[j]);
         }
       }
@@ -179,11 +154,6 @@ __global__ __launch_bounds__(NTHREADS) void k_form_buffer(FormArgs a) {
   }
   const double s = block_sum(acc);
   if (threadIdx.x == 0) a.part[l][lb] = s;
-  if constexpr (!BF16) {
-    if (pm == nullptr) return;
-    mx = block_max(mx);
-    if (threadIdx.x == 0) pm[lb] = mx;
-  }
 }
 
 template <bool BF16>
@@ -247,38 +217,19 @@ __global__ __launch_bounds__(GATE_THREADS) void k_gate(GateArgs a) {
   const double* p = a.parts + static_cast<long long>(l) * a.nparts_stride;
   const int np = a.nparts[l];
   double s = 0.0;
-  float mx = 0.0f;
-  // a layer of 67M elements has 16384 partials: eight loads of each kind in
-  // flight per thread, added in the same order as one by one
-  const float* pm = a.tab ? a.tab[l].pmax : nullptr;
+  // a layer of 67M elements has 16384 partials: eight loads in flight per
+  // thread, added in the same order as one by one
   constexpr int U = 8;
   int i = threadIdx.x;
   for (; i + (U - 1) * GATE_THREADS < np; i += U * GATE_THREADS) {
     double v[U];
-    float w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      v[u] = p[i + u * GATE_THREADS];
-      w[u] = pm != nullptr ? pm[i + u * GATE_THREADS] : 0.0f;
-    }
+    for (int u = 0; u < U; ++u) v[u] = p[i + u * GATE_THREADS];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      s += v[u];
-      mx = fmaxf(mx, w[u]);
-    }
+    for (int u = 0; u < U; ++u) s += v[u];
   }
-  for (; i < np; i += GATE_THREADS) {
-    s += p[i];
-    if (pm != nullptr) mx = fmaxf(mx, pm[i]);
-  }
+  for (; i < np; i += GATE_THREADS) s += p[i];
   s = block_sum(s);
-  if (pm != nullptr) {
-    mx = block_max(mx);
-    if (threadIdx.x == 0) {
-      a.tab[l].amax[0] = mx;
-      a.tab[l].amax[1] = isfinite(s) ? 0.0f : 1.0f;
-    }
-  }
   double* out_rm = reinterpret_cast<double*>(a.out + 1);
   if (threadIdx.x == 0) {
     const double nb = sqrt(s);

@@ -42,4 +42,17 @@ inline std::vector<std::vector<int>> plan_stream_batches(const std::vector<long 
   return out;
 }
 
+// Tiles of the pass that finds every row's and column's largest value
+// (k_gemm_i8.hip): the narrowest of 256, 512 and 1024 columns that make at most
+// 32 tiles across, and at most 32 tiles down: a row or a column then has at most
+// 32 partial maxima to join (a row of more than 32768 columns has more).  False when a row's partial maxima
+// and its maximum, or a column's, do not fit in r values.
+inline bool plan_range(int m, int n, int r, int* tr, int* tc) {
+  *tc = 256;
+  while ((n - 1) / *tc + 1 > 32 && *tc < 1024) *tc *= 2;
+  *tr = 32;
+  while ((m - 1) / *tr + 1 > 32) *tr *= 2;
+  return r >= 32 && (n - 1) / *tc + 1 < r;
+}
+
 }  // namespace cd

@@ -1,13 +1,26 @@
-// Prints the streaming-pass launch plan of the C ABI for the layer shapes read
-// from stdin ("m n" per line): one line per launch, "<layers> <blocks>".
+// Prints launch plans of the C ABI, one line per launch or input line, for the
+// sizes read from stdin.  No argument: the streaming passes' launches for layer
+// shapes "m n", "<layers> <blocks>" each; "range": the tiles of the pass for
+// row and column maxima for "m n r", "<ok> <tr> <tc>".
 // Built by the CPU tests with a plain C++ compiler against the library's
 // planning header (it has no HIP dependency).
 #include <cstdio>
+#include <cstring>
 #include <vector>
 
 #include "plan.hpp"
 
-int main() {
+int main(int argc, char** argv) {
+  const char* mode = argc > 1 ? argv[1] : "";
+  if (!std::strcmp(mode, "range")) {
+    int m, n, r;
+    while (std::scanf("%d %d %d", &m, &n, &r) == 3) {
+      int tr = 0, tc = 0;
+      const bool ok = cd::plan_range(m, n, r, &tr, &tc);
+      std::printf("%d %d %d\n", ok ? 1 : 0, tr, tc);
+    }
+    return 0;
+  }
   std::vector<long long> numel;
   long long m, n;
   while (std::scanf("%lld %lld", &m, &n) == 2) numel.push_back(m * n);

@@ -157,16 +157,35 @@ def test_plain_c_client_check():
     assert out.stdout.count("CD_EINVAL") == 8
 
 
-def _stream_plan(shapes, tmp_path):
-    """Streaming-pass launches the library plans for `shapes`: the planning
-    header compiled with g++ (it has no HIP dependency) and run on the CPU."""
+def _plan(tmp_path, lines, *mode):
+    """Launch plans of the library: the planning header compiled with g++ (it
+    has no HIP dependency) and run on the CPU."""
     exe = tmp_path / "plan_check"
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I",
                     os.path.join(ROOT, "paper_2512_13728_amd", "csrc"),
                     os.path.join(ROOT, "tests", "c", "plan_check.cpp"), "-o", str(exe)], check=True)
-    out = subprocess.run([str(exe)], input="".join(f"{m} {n}\n" for m, n in shapes),
+    out = subprocess.run([str(exe), *mode], input="".join(" ".join(map(str, v)) + "\n" for v in lines),
                          capture_output=True, text=True, check=True).stdout
     return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+
+
+def _stream_plan(shapes, tmp_path):
+    """Streaming-pass launches the library plans for `shapes`."""
+    return _plan(tmp_path, shapes)
+
+
+def test_range_tiles_fit_the_workspace(tmp_path):
+    """The pass that finds B's row and column maxima leaves ceil(n / tc)
+    partials and the maximum of every row in P's place (m r floats) and
+    ceil(m / tr) partials of every column in R's (n r): both fit whatever the
+    size, at the least rank that takes the pass; a row with too many partials
+    is refused.  The tiles are those the kernels are built for."""
+    sizes = [(m, n, r) for r in (33, 64, 1024) for m in (33, 64, 65, 1024, 1025, 50304, 2 ** 22) for n in (33, 257, 8192, 8193, 16385, 32768, 32769, 2 ** 20)]
+    for (m, n, r), (ok, tr, tc) in zip(sizes, _plan(tmp_path, sizes, "range")):
+        assert tc in (256, 512, 1024) and tr % 32 == 0
+        across, down = -(-n // tc), -(-m // tr)
+        assert down <= 32 <= r and (across <= 32 or tc == 1024)
+        assert ok == (across + 1 <= r), (m, n, r)
 
 
 def test_streaming_launch_plan_of_the_workloads(tmp_path):
