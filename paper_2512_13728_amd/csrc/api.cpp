@@ -998,7 +998,10 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
   }
   cd::PlaneArgs pa{};   // the planes of P, in the same launch
   pa.rows = m; pa.r = r; pa.rp = rp; pa.S = up; pa.f16 = f16;
-  for (int j = 0; j < nl; ++j) { pa.src[j] = lay(j)->P; pa.dst[j] = lay(j)->planes; }
+  for (int j = 0; j < nl; ++j) {
+    pa.src[j] = lay(j)->P; pa.dst[j] = lay(j)->planes;
+    pa.exps[j] = reinterpret_cast<int*>(lay(j)->pa);   // 4 m bytes: the fp64 P has been used for R
+  }
   st = run(g, K_COLNORM, ((12.0 + 4.0 * cn.S) * nr + (vec_update ? 0.0 : (4.0 + 2.0 * up) * mr)) * nl, 3.0 * nr * nl, s,
            [&] { return cd::launch_colnorm(cn, vec_update ? nullptr : &pa, nl, s); });
   if (st != CD_OK) return st;
@@ -1039,6 +1042,7 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
     ua.R[j] = lay(j)->planes + 3LL * m * rp;
     ua.Q[j] = lay(j)->planes + 3LL * m * rp + 3LL * n * rp;
     ua.exps[j] = cn.exps[j];
+    ua.pexps[j] = pa.exps[j];
   }
   return run(g, fast ? K_UPDATE_BF1 : (f16 ? K_UPDATE_F16 : K_UPDATE), ub, 4.0 * mn * r * nl, s,
              [&] { return cd::launch_update_planes(ua, nl, up, s); });

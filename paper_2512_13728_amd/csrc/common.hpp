@@ -306,8 +306,8 @@ struct ColnormArgs {
   float* Q[MAXB];                  // out: n x r
   // bf16 planes (pieces S, row stride rp) of R and of Q for the update
   int S, rp;
-  // f16: S = 2 fp16 pieces instead, every row of R and of Q scaled by a power
-  // of two that takes its largest finite value into [2^13, 2^14)
+  // f16: S = 2 fp16 pieces instead, every row of R, of Q and of P scaled by a
+  // power of two that takes its largest finite value into [2^13, 2^14)
   bool f16;
   int* exps[MAXB];                 // f16: out, n exponents of R's rows, then n of Q's
   __bf16* Rpl[MAXB];
@@ -386,14 +386,13 @@ bool update_vec_fits(int r);
 hipError_t launch_update_vec(UpdateVecArgs a, int nl, hipStream_t s);
 // bf16 planes of fp32 matrices (rows x r): plane s (s < S <= 3) holds the
 // s-th bf16 piece of each value, rows padded to rp (multiple of 32) with zeros.
-// f16: S = 2 fp16 pieces of 2^F16_PEXP times the value (|P| < 8: an orthonormal
-// panel's entries are at most 1).
-constexpr int F16_PEXP = 13;
+// f16: S = 2 scaled fp16 pieces, the rows' exponents in exps.
 struct PlaneArgs {
   int rows, r, rp, S;
   bool f16;
   const float* src[MAXB];
   __bf16* dst[MAXB];               // S * rows * rp elements
+  int* exps[MAXB];                 // f16: out, rows exponents
 };
 
 // The update from planes of P (m x rp), R and Q (n x rp): pieces = 3 forms
@@ -409,6 +408,7 @@ struct UpdatePlArgs {
   const __bf16* R[MAXB];
   const __bf16* Q[MAXB];
   const int* exps[MAXB];           // fp16 pieces: the exponents of R's rows, then of Q's
+  const int* pexps[MAXB];          // and of P's
   // spec = 1: the buffer pass already applied the skip branch's
   // X = xdecay X - eta_local G (the decay included); the update first adds
   // gc G back (gc = eta_local; no read of G when it is 0).  spec = 0: the
@@ -426,7 +426,10 @@ struct UpdatePlArgs {
 // many fp32 additions: the relative error of X after a step from X = 0,
 // against float64, is 1.20e-7 (bf16 pieces: 1.07e-7) at r = 64, 1.36e-7
 // (1.38e-7) at 96, 1.56e-7 (1.72e-7) at 130, 1.76e-7 (2.05e-7) at 192, 2.6e-7
-// (3.4e-7) at 512, 3.6e-7 (4.9e-7) at 1024.  Up to 128 the update streams M and
+// (3.4e-7) at 512, 3.6e-7 (4.9e-7) at 1024.  Rows of P and of R and Q have scales
+// of their own, so this holds in every row and column of the correction (with
+// one scale for P, rows of 1e-6 were 9e-5 off and rows of 1e-10 lost); an entry
+// more than 2^16 below its row's largest keeps 2^-39 of that.  Up to 128 the update streams M and
 // X and gains nothing (28M parameters at r = 96: 0.77 ms a step, 0.76 with bf16
 // pieces); above, the products count.
 inline bool update_f16_fits(int r) { return r > 128; }

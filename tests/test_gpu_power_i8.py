@@ -142,9 +142,10 @@ def _row_err(a, b):
 # every row and every column of B has a scale of its own: with half of them
 # 2^-40 of the others (a layer-wide scale would leave them 7 bits), each row of
 # P, R, Q, dM and dX and each column of dM and dX is still as accurate as fp32
-# state allows.  r = 32 takes the fp64 MFMA.  The reference applies the inverse
+# state allows.  r = 32 takes the fp64 MFMA, r = 160 the update from fp16
+# pieces.  The reference applies the inverse
 # factor to the rows of P~, as a Householder QR is not accurate row by row.
-@pytest.mark.parametrize("r", [32, 48, 97])
+@pytest.mark.parametrize("r", [32, 48, 97, 160])
 @pytest.mark.parametrize("kind", ["rows", "columns", "both"])
 @pytest.mark.parametrize("m,n", [(512, 640), (509, 643)])
 def test_small_rows_and_columns(m, n, kind, r):
