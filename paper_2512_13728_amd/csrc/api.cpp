@@ -210,9 +210,10 @@ struct cd_layer {
   // Products on the int8 MFMA (fp32-gradient layers).  The digit planes of Q
   // lie over P1 and the update's planes (neither is written before P~ is
   // complete), those of P over the same (P1 is dead, the planes come after
-  // R).  B's row maxima lie in P's place and the partial column maxima in R's
-  // (both are written later in the step), the column maxima in colsq's
-  // (4 n bytes of at least 4.1 n; their last use is R).
+  // R).  B's row maxima lie in P's place (4 m bytes; it is written later in
+  // the step), the column maxima in colsq's (4 n bytes of at least 4.1 n; their
+  // last use is R), and the partial maxima of both where P~'s partial products
+  // come next.
   char* digits() const { return reinterpret_cast<char*>(pb); }
   float* cmax() const { return reinterpret_cast<float*>(colsq); }
 };
@@ -752,7 +753,10 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
     *done = false;
     cd::I8Args ia{};
     cd::RangeArgs ra8{};
-    if (r < cd::I8_RMIN || !cd::plan_range(m, n, r, &ra8.tr, &ra8.tc)) return CD_OK;
+    size_t room = ~static_cast<size_t>(0) >> 1;
+    for (int j = 0; j < nl; ++j) room = std::min(room, lay(j)->split_cap);
+    if (r < cd::I8_RMIN || !cd::plan_range(m, n, static_cast<long long>(room / sizeof(float)), &ra8.tr, &ra8.tc))
+      return CD_OK;
     for (const bool other : {true, false}) {   // the other product's plan, then this one's
       const int Mp = first != other ? m : n, Kp = first != other ? n : m;
       if (!plan_i8(Mp, r, Kp, nl, conc, &ia.splits, &ia.kchunk)) return CD_OK;
@@ -769,8 +773,8 @@ cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>
       ra8.m = m; ra8.n = n; ra8.run_if = run_if;
       for (int j = 0; j < nl; ++j) {
         ra8.B[j] = static_cast<const float*>(Aof(j));
-        ra8.rows[j] = lay(j)->P;
-        ra8.cols[j] = lay(j)->R;
+        ra8.part[j] = static_cast<float*>(lay(j)->split_part);
+        ra8.rmax[j] = lay(j)->P;
         ra8.cmax[j] = lay(j)->cmax();
       }
       st2 = run(g, K_RANGE8, 4.0 * mnd * nl, 0.0, s, [&] { return cd::launch_range8(ra8, nl, s); });

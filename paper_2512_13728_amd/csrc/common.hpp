@@ -197,13 +197,13 @@ inline size_t i8_bytes(int N, int splits, int kchunk) {
 inline int gemm_i8_bn(int N) { return (N + 31) / 32 % 4 == 0 || N > 512 ? 128 : 64; }
 inline int gemm_i8_bm(int N) { return 8192 / gemm_i8_bn(N); }
 // The largest |B| of every row and column of B (m x n): launch_range8 leaves
-// partial maxima per tile of tr x tc, which launch_slice8 joins when it is given
-// the same arguments.
+// partial maxima per tile of tr x tc (plan_range) in part, which launch_slice8
+// joins when it is given the same arguments.
 struct RangeArgs {
   int m, n, tr, tc;
   const float* B[MAXB];
-  float* rows[MAXB];               // m maxima, then partials [ceil(n / tc)][m]
-  float* cols[MAXB];               // partials [ceil(m / tr)][n]
+  float* part[MAXB];               // [tiles across][m] unless there is one, then [tiles down][n]
+  float* rmax[MAXB];               // m maxima
   float* cmax[MAXB];               // n maxima
   const int* run_if;
 };

@@ -43,16 +43,27 @@ inline std::vector<std::vector<int>> plan_stream_batches(const std::vector<long 
 }
 
 // Tiles of the pass that finds every row's and column's largest value
-// (k_gemm_i8.hip): the narrowest of 256, 512 and 1024 columns that make at most
-// 32 tiles across, and at most 32 tiles down: a row or a column then has at most
-// 32 partial maxima to join (a row of more than 32768 columns has more).  False when a row's partial maxima
-// and its maximum, or a column's, do not fit in r values.
-inline bool plan_range(int m, int n, int r, int* tr, int* tc) {
+// (k_gemm_i8.hip): the narrowest of 256, 512 and 1024 columns that make at most 32
+// across, and as many tiles down as make at most 2048 in all (eight per CU) and
+// at most 256 partial maxima per column to join.  `room`: values that the
+// partials may take, m per tile across (none for one tile: those are the maxima)
+// and n per tile down; false when they cannot fit.
+inline long long range_partials(int m, int n, int tr, int tc) {
+  const long long across = (n - 1) / tc + 1, down = (m - 1) / tr + 1;
+  return (across == 1 ? 0 : across * m) + down * n;
+}
+inline bool plan_range(int m, int n, long long room, int* tr, int* tc) {
   *tc = 256;
   while ((n - 1) / *tc + 1 > 32 && *tc < 1024) *tc *= 2;
+  const long long across = (n - 1) / *tc + 1;
   *tr = 32;
-  while ((m - 1) / *tr + 1 > 32) *tr *= 2;
-  return r >= 32 && (n - 1) / *tc + 1 < r;
+  for (;;) {
+    const long long down = (m - 1) / *tr + 1;
+    const bool fits = range_partials(m, n, *tr, *tc) <= room;
+    if (down == 1) return fits;
+    if (fits && down <= 256 && across * down <= 2048) return true;
+    *tr *= 2;
+  }
 }
 
 }  // namespace cd

@@ -1,7 +1,7 @@
 // Prints launch plans of the C ABI, one line per launch or input line, for the
 // sizes read from stdin.  No argument: the streaming passes' launches for layer
 // shapes "m n", "<layers> <blocks>" each; "range": the tiles of the pass for
-// row and column maxima for "m n r", "<ok> <tr> <tc>".
+// row and column maxima for "m n room", "<ok> <tr> <tc> <partials>".
 // Built by the CPU tests with a plain C++ compiler against the library's
 // planning header (it has no HIP dependency).
 #include <cstdio>
@@ -13,11 +13,12 @@
 int main(int argc, char** argv) {
   const char* mode = argc > 1 ? argv[1] : "";
   if (!std::strcmp(mode, "range")) {
-    int m, n, r;
-    while (std::scanf("%d %d %d", &m, &n, &r) == 3) {
+    int m, n;
+    long long room;
+    while (std::scanf("%d %d %lld", &m, &n, &room) == 3) {
       int tr = 0, tc = 0;
-      const bool ok = cd::plan_range(m, n, r, &tr, &tc);
-      std::printf("%d %d %d\n", ok ? 1 : 0, tr, tc);
+      const bool ok = cd::plan_range(m, n, room, &tr, &tc);
+      std::printf("%d %d %d %lld\n", ok ? 1 : 0, tr, tc, cd::range_partials(m, n, tr, tc));
     }
     return 0;
   }

@@ -175,17 +175,22 @@ def _stream_plan(shapes, tmp_path):
 
 
 def test_range_tiles_fit_the_workspace(tmp_path):
-    """The pass that finds B's row and column maxima leaves ceil(n / tc)
-    partials and the maximum of every row in P's place (m r floats) and
-    ceil(m / tr) partials of every column in R's (n r): both fit whatever the
-    size, at the least rank that takes the pass; a row with too many partials
-    is refused.  The tiles are those the kernels are built for."""
-    sizes = [(m, n, r) for r in (33, 64, 1024) for m in (33, 64, 65, 1024, 1025, 50304, 2 ** 22) for n in (33, 257, 8192, 8193, 16385, 32768, 32769, 2 ** 20)]
-    for (m, n, r), (ok, tr, tc) in zip(sizes, _plan(tmp_path, sizes, "range")):
-        assert tc in (256, 512, 1024) and tr % 32 == 0
+    """The pass that finds B's row and column maxima leaves its partial maxima
+    where P~'s partial products come next, at least 8 max(m, n) r bytes, r >=
+    33: they fit whatever the shape, the tiles are those the kernels are built
+    for, and a tall or a wide matrix has enough of them to fill the chip, as
+    far as it has 32-row tiles and a column at most 256 partials to join.  Less
+    room makes the tiles taller, none refuses."""
+    sizes = [(m, n, 2 * max(m, n) * 33) for m in (33, 64, 65, 1025, 4096, 50304, 65536, 2 ** 22)
+             for n in (33, 256, 257, 8192, 8193, 16385, 32769, 2 ** 20) if m * n <= 2 ** 36]
+    for (m, n, room), (ok, tr, tc, parts) in zip(sizes, _plan(tmp_path, sizes, "range")):
+        assert ok and tc in (256, 512, 1024) and tr % 32 == 0, (m, n)
         across, down = -(-n // tc), -(-m // tr)
-        assert down <= 32 <= r and (across <= 32 or tc == 1024)
-        assert ok == (across + 1 <= r), (m, n, r)
+        assert parts == (across * m if across > 1 else 0) + down * n <= room, (m, n)
+        assert down <= 256 and (across <= 32 or tc == 1024)
+        assert across * down >= min(256, -(-m // 32) * across, 128 * across), (m, n, tr, tc)
+    tight = [(4096, 4096, v) for v in (4096 * 48, 4096 * 17, 4096 * 17 - 1, 0)]
+    assert [row[:3] for row in _plan(tmp_path, tight, "range")] == [(1, 128, 256), (1, 4096, 256), (0, 4096, 256), (0, 4096, 256)]
 
 
 def test_streaming_launch_plan_of_the_workloads(tmp_path):

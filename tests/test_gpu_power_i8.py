@@ -23,10 +23,12 @@ pytestmark = pytest.mark.gpu
 # the narrowest rank of the path and the one below it; column blocks of 32,
 # tiles of 64 and 128 columns whole and partial; K of one stage and one past
 # it, several slices, slices with a partial last chunk; rows not a multiple of
-# four (unaligned loads); tall and wide
+# four (unaligned loads); tall and wide; every width of the tiles that find B's
+# row and column maxima
 @pytest.mark.parametrize("m,n,r", [
     (260, 257, 32), (260, 257, 33), (129, 64, 64), (64, 129, 64), (65, 66, 65), (127, 1030, 96),
     (1030, 127, 97), (200, 2051, 128), (2051, 200, 129), (150, 5000, 34), (5000, 150, 34), (600, 700, 320),
+    (64, 9001, 33), (40, 33000, 33), (40, 40001, 33), (20000, 64, 40),
 ])
 def test_power_product_edges(m, n, r):
     w = S.small_workload(m, n, r, k=min(24, r - 1), stream_id=700 + r)
