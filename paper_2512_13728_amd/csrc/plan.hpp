@@ -42,6 +42,17 @@ inline std::vector<std::vector<int>> plan_stream_batches(const std::vector<long 
   return out;
 }
 
+// Workgroups across the launch that normalises R (n rows) and cuts the planes of P
+// (m rows) beside it: as many as the larger of the two has work for, `per` rows
+// or quads each, at most `most`, the smaller one's last ones idle.  Planned for n
+// alone, the 65536 rows of P of a 65536 x 256 layer at r = 192 went through 64
+// workgroups: 266 us, 24 with 4096 (a launch of its own 52); r = 96 in bf16 162,
+// now 10.
+inline long long colnorm_blocks(long long n, long long m, long long per, long long most) {
+  const long long b = ((n > m ? n : m) + per - 1) / per;
+  return b < most ? b : most;
+}
+
 // Tiles of the pass that finds every row's and column's largest value
 // (k_gemm_i8.hip): the narrowest of 256, 512 and 1024 columns that make at most 32
 // across, and as many tiles down as make at most 2048 in all (eight per CU) and

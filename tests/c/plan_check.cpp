@@ -1,7 +1,8 @@
 // Prints launch plans of the C ABI, one line per launch or input line, for the
 // sizes read from stdin.  No argument: the streaming passes' launches for layer
 // shapes "m n", "<layers> <blocks>" each; "range": the tiles of the pass for
-// row and column maxima for "m n room", "<ok> <tr> <tc> <partials>".
+// row and column maxima for "m n room", "<ok> <tr> <tc> <partials>"; "colnorm":
+// workgroups of the launch that normalises R and cuts P for "n m per most".
 // Built by the CPU tests with a plain C++ compiler against the library's
 // planning header (it has no HIP dependency).
 #include <cstdio>
@@ -20,6 +21,12 @@ int main(int argc, char** argv) {
       const bool ok = cd::plan_range(m, n, room, &tr, &tc);
       std::printf("%d %d %d %lld\n", ok ? 1 : 0, tr, tc, cd::range_partials(m, n, tr, tc));
     }
+    return 0;
+  }
+  if (!std::strcmp(mode, "colnorm")) {
+    long long n, m, per, most;
+    while (std::scanf("%lld %lld %lld %lld", &n, &m, &per, &most) == 4)
+      std::printf("%lld\n", cd::colnorm_blocks(n, m, per, most));
     return 0;
   }
   std::vector<long long> numel;

@@ -193,6 +193,15 @@ def test_range_tiles_fit_the_workspace(tmp_path):
     assert [row[:3] for row in _plan(tmp_path, tight, "range")] == [(1, 128, 256), (1, 4096, 256), (0, 4096, 256), (0, 4096, 256)]
 
 
+def test_colnorm_launch_has_work_for_the_taller_of_r_and_p(tmp_path):
+    """The launch that normalises R (n rows) also cuts the planes of P (m rows):
+    its workgroups are planned for the larger, so that a tall matrix's P does
+    not go through the few that its short R needs."""
+    rows = [(256, 65536, 4, 4096), (65536, 256, 4, 4096), (256, 1000, 4, 4096), (1, 0, 4, 4096),
+            (256 * 24, 65536 * 24, 256, 4096), (100, 2 ** 31, 4, 4096)]
+    assert _plan(tmp_path, rows, "colnorm") == [(4096,), (4096,), (250,), (1,), (4096,), (4096,)]
+
+
 def test_streaming_launch_plan_of_the_workloads(tmp_path):
     """The buffer pass and the local update launch whole layers in group order,
     at most 48 layers and 98304 blocks of 4096 elements per launch: the

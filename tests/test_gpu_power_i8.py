@@ -24,11 +24,13 @@ pytestmark = pytest.mark.gpu
 # tiles of 64 and 128 columns whole and partial; K of one stage and one past
 # it, several slices, slices with a partial last chunk; rows not a multiple of
 # four (unaligned loads); tall and wide; every width of the tiles that find B's
-# row and column maxima
+# row and column maxima; more rows of P or of R than the launch that cuts them
+# has waves
 @pytest.mark.parametrize("m,n,r", [
     (260, 257, 32), (260, 257, 33), (129, 64, 64), (64, 129, 64), (65, 66, 65), (127, 1030, 96),
     (1030, 127, 97), (200, 2051, 128), (2051, 200, 129), (150, 5000, 34), (5000, 150, 34), (600, 700, 320),
     (64, 9001, 33), (40, 33000, 33), (40, 40001, 33), (20000, 64, 40),
+    (20000, 135, 130), (135, 20000, 130),
 ])
 def test_power_product_edges(m, n, r):
     w = S.small_workload(m, n, r, k=min(24, r - 1), stream_id=700 + r)
