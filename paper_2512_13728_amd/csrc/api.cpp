@@ -232,6 +232,7 @@ struct Unit {
   std::vector<int> sel;  // positions in the group
   int fbq_splits = 1, fbq_kchunk = 0;   // K slices of the fused buffer pass + P~ = B Q
   int off;               // first factor-table entry
+  int conc = 1;          // units its K slices are planned for (plan_conc)
 };
 
 struct cd_group {
@@ -507,6 +508,12 @@ void plan_group(cd_group* g, cd_layer* const* layers, int n, std::vector<int>& n
       g->units.push_back(std::move(u));
     }
   }
+  const int nu = static_cast<int>(g->units.size());
+  g->nside = std::min(nu - 1, cd_group::NSIDE);
+  std::vector<long long> work(nu);
+  for (int u = 0; u < nu; ++u)
+    work[u] = 1LL * g->shapes[g->units[u].sc].m * g->shapes[g->units[u].sc].n * static_cast<long long>(g->units[u].sel.size());
+  for (int u = 0; u < nu; ++u) g->units[u].conc = cd::plan_conc(work.data(), nu, u, g->nside);
   // the fused buffer pass + P~ = B Q of bf16-gradient layers: K slices per
   // unit, so that a launch has about three workgroups per CU (one fits) and
   // a slice keeps at least 512 k
@@ -565,8 +572,7 @@ cd_status build_group(cd_layer* const* layers, int n, cd_group** out) {
     e = hipMemcpy(g->nparts_fx, g->np_fx.data(), sizeof(int) * n, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(g->prev, pv.data(), sizeof(double*) * n, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(g->chol_tab, ct.data(), sizeof(cd::CholTab) * n, hipMemcpyHostToDevice);
-  if (g->units.size() > 1) {
-    g->nside = std::min(static_cast<int>(g->units.size()) - 1, cd_group::NSIDE);
+  if (g->nside > 0) {
     if (e == hipSuccess) e = hipEventCreateWithFlags(&g->fork_ev, hipEventDisableTiming);
     for (int i = 0; i < g->nside && e == hipSuccess; ++i) {
       e = hipStreamCreateWithFlags(&g->side[i], hipStreamNonBlocking);
@@ -616,7 +622,7 @@ cd_status run(cd_group* g, int kind, double bytes, double flops, hipStream_t s, 
   return CD_OK;
 }
 
-// One stage of the sync branch for the layers `sel` (all of one shape):
+// One stage of the sync branch for the layers of a unit:
 //   0: P~ = B Q          1: Gram matrix of CholQR pass 0 (fp64)
 //   2: pass-0 apply, bf16-gradient layers: P1 = P~ U (bf16 x 6, U = T^-1 in fp32)
 //   3: Gram matrix of pass 1 (fp64 for fp32 layers; bf16 x 6 for bf16-gradient
@@ -630,13 +636,13 @@ cd_status run(cd_group* g, int kind, double bytes, double flops, hipStream_t s, 
 // 0, 1, or 2 = as the control word says.  run_if: NULL, or &ctl->flag when
 // the branch is enqueued before the decision is known (every kernel then
 // returns at once on a local step).
-cd_status enqueue_sync(cd_group* g, const ShapeClass& sc, const std::vector<int>& sel,
-                       const void* const* G, int spec,
+cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int spec,
                        float* const* M, float* const* X, float* const* Q, float mu, float eta,
                        int r, int stage, hipStream_t s, const int* run_if) {
-  const int m = sc.m, n = sc.n, nl = static_cast<int>(sel.size());
+  const std::vector<int>& sel = unit.sel;
+  const int m = g->shapes[unit.sc].m, n = g->shapes[unit.sc].n, nl = static_cast<int>(sel.size());
   auto lay = [&](int j) { return g->layers[sel[j]]; };
-  const int conc = 1 + g->nside;   // units whose stages run side by side
+  const int conc = unit.conc;
   // small layers: four launches (see below), their products without split-K
   const bool small = cd::small_sync_fits(m, n, r);
 
@@ -1282,7 +1288,7 @@ cd_status enqueue_branch(cd_group* g, int branch, int spec, const void* const* G
       for (int ui = 0; ui < nu; ++ui) {
         const Unit& u = g->units[ui];
         const hipStream_t su = stream_of(ui);
-        cd_status st = enqueue_sync(g, g->shapes[u.sc], u.sel, G, uspec, M, X, Q, mu, eta, r, stage, su, run_if);
+        cd_status st = enqueue_sync(g, u, G, uspec, M, X, Q, mu, eta, r, stage, su, run_if);
         if (st != CD_OK) return st;
         if (cd::small_sync_fits(g->shapes[u.sc].m, g->shapes[u.sc].n, r)) continue;
         if (stage == 1 || stage == 3) {
@@ -1517,6 +1523,7 @@ void plan_static(cd_group* g, cd_layer* L) {
   u.sel.resize(1);
   u.sel[0] = 0;
   u.off = 0;
+  u.conc = 1;
   g->sbatches.resize(1);
   g->sbatches[0].resize(1);
   g->sbatches[0][0] = 0;

@@ -42,6 +42,21 @@ inline std::vector<std::vector<int>> plan_stream_batches(const std::vector<long 
   return out;
 }
 
+// How many units' launches a unit's K slices are planned for, where units 0 ..
+// nu-1 of work[u] values each run side by side on nside + 1 streams: all of
+// them, but one where all the others together have less than 1/128 of the
+// unit's work and are gone before its products.  4096 x 8192 with fp32 gradients
+// beside 256 x 256, 128 x 128 and 100 x 100 (1/360), r = 96: sync step 769 us
+// planned for four, 665 for one; 4096 x 16384 beside 64 x 64, 80 x 80 and 96 x
+// 96, r = 64: 918 and 848, bf16 720 and 667.  But with others of 1/64 and more the fewer
+// slices are the better: 4096 x 4096 beside 512 x 512, r = 256: 662 us planned
+// for two, 691 for one, bf16 525 and 544.
+inline int plan_conc(const long long* work, int nu, int u, int nside) {
+  long long others = 0;
+  for (int i = 0; i < nu; ++i) others += i == u ? 0 : work[i];
+  return 128 * others < work[u] ? 1 : 1 + nside;
+}
+
 // Workgroups across the launch that normalises R (n rows) and cuts the planes of P
 // (m rows) beside it: as many as the larger of the two has work for, `per` rows
 // or quads each, at most `most`, the smaller one's last ones idle.  Planned for n

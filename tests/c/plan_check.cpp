@@ -2,11 +2,13 @@
 // sizes read from stdin.  No argument: the streaming passes' launches for layer
 // shapes "m n", "<layers> <blocks>" each; "range": the tiles of the pass for
 // row and column maxima for "m n room", "<ok> <tr> <tc> <partials>"; "colnorm":
-// workgroups of the launch that normalises R and cuts P for "n m per most".
+// workgroups of the launch that normalises R and cuts P for "n m per most";
+// "conc": units that unit u of the given work is planned for, "nside u work ...".
 // Built by the CPU tests with a plain C++ compiler against the library's
 // planning header (it has no HIP dependency).
 #include <cstdio>
 #include <cstring>
+#include <sstream>
 #include <vector>
 
 #include "plan.hpp"
@@ -27,6 +29,19 @@ int main(int argc, char** argv) {
     long long n, m, per, most;
     while (std::scanf("%lld %lld %lld %lld", &n, &m, &per, &most) == 4)
       std::printf("%lld\n", cd::colnorm_blocks(n, m, per, most));
+    return 0;
+  }
+  if (!std::strcmp(mode, "conc")) {
+    char line[4096];
+    while (std::fgets(line, sizeof line, stdin)) {
+      std::istringstream in(line);
+      int nside, u;
+      long long w;
+      std::vector<long long> work;
+      in >> nside >> u;
+      while (in >> w) work.push_back(w);
+      std::printf("%d\n", cd::plan_conc(work.data(), static_cast<int>(work.size()), u, nside));
+    }
     return 0;
   }
   std::vector<long long> numel;

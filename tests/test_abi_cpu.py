@@ -202,6 +202,16 @@ def test_colnorm_launch_has_work_for_the_taller_of_r_and_p(tmp_path):
     assert _plan(tmp_path, rows, "colnorm") == [(4096,), (4096,), (250,), (1,), (4096,), (4096,)]
 
 
+def test_slices_are_planned_for_the_units_that_share_the_chip(tmp_path):
+    """A unit's K slices are planned for all units side by side, unless the
+    others together have less than 1/128 of its work; a unit alone for itself,
+    a small one beside a large one for all."""
+    big = 4096 * 8192
+    rows = [(3, 0, big, 65536, 16384, 10000), (3, 1, big, 65536, 16384, 10000), (0, 0, big), (1, 0, 128, 1), (1, 0, 129, 1),
+            (3, 2, 768 * 2304, 768 * 768, 768 * 3072, 3072 * 768)]
+    assert _plan(tmp_path, rows, "conc") == [(1,), (4,), (1,), (2,), (1,), (4,)]
+
+
 def test_streaming_launch_plan_of_the_workloads(tmp_path):
     """The buffer pass and the local update launch whole layers in group order,
     at most 48 layers and 98304 blocks of 4096 elements per launch: the
