@@ -702,12 +702,12 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
   auto part = [&](int j) { return lay(j)->split_part; };
   // The Gram matrix of an fp64 panel (P~, then P1) of fp32-gradient layers on
   // the int8 MFMA, its digit planes in `room` (bytes `cap`), which the panel
-  // does not use.  done = false: it stays on the fp64 MFMA (see I8_GRAM_RMIN;
+  // does not use.  done = false: it stays on the fp64 MFMA (see I8_GRAM_ALWAYS;
   // or no room).
   auto gram_i8 = [&](auto Pof, auto room, auto cap, bool* done) -> cd_status {
     *done = false;
     cd::I8Args ia{};
-    if (r < cd::I8_GRAM_RMIN || nl * conc > cd::I8_GRAM_LAYERS) return CD_OK;
+    if (r < cd::I8_GRAM_ALWAYS && (r < cd::I8_GRAM_RMIN || conc == 1 || m >= cd::I8_GRAM_ROWS)) return CD_OK;
     long long tiles = 0;   // 128 x 64, not wholly below the diagonal
     for (int i = 0; i < r; i += 128) tiles += (r - i + 63) / 64;
     tiles *= nl;

@@ -153,15 +153,21 @@ inline bool gemm_acc64(GemmKind k) { return k != GemmKind::F32; }
 // digit planes by launch_slice8 first.  K is split in `splits` slices of
 // kchunk (a multiple of 64, at most I8_KMAX: the int32 sums stay exact).
 constexpr int I8_RMIN = 33;        // narrower products stay on the fp64 MFMA kernel
-// Gram matrices take it from this rank on (one 64 x 64 tile and less: the fp64
-// kernel, 18 us at 4096 x 64), and up to this many layers in flight over the
-// units that run side by side: 4096 x 1024 197 -> 95 us (with its digits 110),
-// the sync step of four 4-layer units at r = 96 0.746 -> 0.724 ms, of four
-// 2-layer ones at r = 130 0.669 -> 0.648; but four 12-layer units at r = 192 went
-// from 2.16 to 2.20, as a workgroup of this kernel needs a whole CU's LDS and
-// waits for the other units' workgroups to leave one.
+// Gram matrices take it at I8_GRAM_ALWAYS columns and more, where multiplying
+// bounds them (fp64 MFMA / int8 sync steps: 1024 x 1024, r = 512, 8 layers 1098 /
+// 1032 us, 16 layers 1777 / 1624; two 2048-wide blocks, r = 512, 4497 / 4280; r =
+// 384 0.98 to 1.04 times), and from I8_GRAM_RMIN to there only where units run
+// side by side and the panel has fewer than I8_GRAM_ROWS rows: the fp64 kernel
+// then has two slices at most, and its long workgroups fill the other units'
+// CUs (odd shapes of two layers each, r = 130, 559 / 541; of eight, 1183 / 1147;
+// 768-wide sets of 1 to 12 blocks, r = 96 and 192: 0.5 to 3% ahead of fp64).
+// Elsewhere the fp64 kernel is level or ahead, as the digits are a launch and a
+// pass of their own: 1024 x 1024, r = 128, one layer 262 / 265, 16 layers 497 /
+// 532; 2048-wide blocks, r = 128, 859 / 882; 768 x 768, r = 128, 32 layers 628 /
+// 653; 1024 x 1024 and 2048 x 1024, r = 128, eight of each 667 / 724.
 constexpr int I8_GRAM_RMIN = 65;
-constexpr int I8_GRAM_LAYERS = 16;
+constexpr int I8_GRAM_ALWAYS = 384;
+constexpr int I8_GRAM_ROWS = 1024;
 struct I8Args {
   int M, N, K, lda;
   int np;                          // N rounded up to 32

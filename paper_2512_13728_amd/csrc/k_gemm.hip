@@ -1,7 +1,7 @@
 // Skinny GEMMs of the Dion power iteration (Algorithm 1 / Algorithm 2, sync
 // branch) on MFMA:
 //   W  = P~^T P~        (Gram matrix, upper tiles only; k_gemm_i8.hip where
-//                        I8_GRAM_RMIN and I8_GRAM_LAYERS allow)
+//                        gram_i8 in api.cpp takes it)
 //   P  = P~ U           (the inverse factor applied, U upper triangular)
 //   P~ = B Q, R = B^T P (fp32-gradient layers at r <= 32, where streaming B
 //                        bounds the product: 75 us at 4096 x 16384, r = 16;
@@ -9,8 +9,9 @@
 //                        took 1.3 ms at r = 1024 where these tiles took 2.5)
 // These run in fp64 (v_mfma_f64_16x16x4_f64 on fp32 or fp64 operands): P~
 // is the ill-conditioned panel, and keeping it, its Gram matrix and the CholQR
-// passes in fp64 makes the orthonormal P accurate to fp32 rounding whatever
-// kappa(P~) is.
+// passes in fp64 makes the orthonormal P accurate to fp32 rounding for any
+// kappa(P~) whose pivots stay above the floor (3e6; the digit products keep
+// 2^-46 of their rows and columns, enough for the same).
 // K can be split over blockIdx.y into partial products that
 // launch_reduce_splits adds in a fixed order (deterministic).
 #include "common.hpp"

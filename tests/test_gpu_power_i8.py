@@ -71,7 +71,7 @@ def test_power_product_scales(kind):
 # their columns completed); a NaN row of R makes every normalised column NaN,
 # an infinite one leaves zeros beside it
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
-@pytest.mark.parametrize("m,n,r", [(300, 200, 48), (130, 515, 64), (300, 200, 97), (390, 515, 130)])
+@pytest.mark.parametrize("m,n,r", [(300, 200, 48), (130, 515, 64), (300, 200, 97), (420, 515, 400)])
 def test_power_product_nonfinite(m, n, r, bad):
     w = S.small_workload(m, n, r, k=24, stream_id=770)
     M, X, Q = (t.cuda().contiguous() for t in S.initial_state(w, 0, device="cpu"))
@@ -124,19 +124,41 @@ def _dominant(m, n, r, f, seed):
     return tuple(t.cuda().contiguous() for t in (G, torch.zeros(m, n), 0.02 * randn(m, n), Q))
 
 
-# the Gram matrix's smallest pivots are 9 to 80 times the floor of 1e-13 of its
-# largest diagonal entry (kappa(P~) up to 4e6), in K slices of 256 rows (one
-# layer) and of all 2048 (13 layers fill the chip)
-@pytest.mark.parametrize("m,n,r,layers,f", [(2048, 512, 256, 1, 1e5), (1024, 1024, 96, 1, 2e5), (2050, 770, 512, 13, 6e4)])
-def test_gram_dominant_row(m, n, r, layers, f):
-    Ls = [cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC) for _ in range(layers)]
-    G, M, X, Q = (list(t) for t in zip(*[_dominant(m, n, r, f, 790 + i) for i in range(layers)]))
+# the smallest pivots of the digit Gram matrix are 5 to 80 times the floor of 1e-13
+# of its largest diagonal entry (kappa(P~) up to 6e6), in K slices of 256 (one
+# layer), 450 and 500 (units side by side) and of all 2050 rows (13 layers fill the
+# chip)
+@pytest.mark.parametrize("shapes,r,f", [([(2048, 512)], 400, 1e5), ([(1000, 1024), (900, 1024)], 96, 2e5), ([(2050, 770)] * 13, 512, 6e4)])
+def test_gram_dominant_row(shapes, r, f):
+    Ls = [cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC) for m, n in shapes]
+    G, M, X, Q = (list(t) for t in zip(*[_dominant(m, n, r, f, 791 + i) for i, (m, n) in enumerate(shapes)]))
     grp = cdl.Group(Ls)
-    _, errs = group_step_and_compare(grp, Ls, G, M, X, Q, 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC, check=[0])
-    d = errs[0]
-    print(f"{m}x{n} r={r} x{layers}", {k: v for k, v in d.items() if k.startswith("err") or k in ("kappa", "orth_P")}, flush=True)
+    check = range(min(2, len(shapes)))
+    _, errs = group_step_and_compare(grp, Ls, G, M, X, Q, 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC, check=check)
+    for i, d in errs.items():
+        print(shapes[i], r, {k: v for k, v in d.items() if k.startswith("err") or k in ("kappa", "orth_P")}, flush=True)
     assert not any(L.rank_deficient() for L in Ls)
-    check_errors(d, False)
+    for d in errs.values():
+        check_errors(d, False)
+
+
+# digit Gram matrices at the edges of their 64- and 128-column tiles and 32-column
+# blocks: below 384 columns where two units run side by side, from there on alone;
+# ragged K slices
+@pytest.mark.parametrize("r", [64, 65, 96, 97, 128, 129, 192, 193, 383, 384, 417, 513])
+def test_gram_edges(r):
+    shapes = [(701, 600), (650, 731)] if r < 384 else [(701, 600)]
+    w = [S.small_workload(m, n, r, k=24, stream_id=870 + r + i) for i, (m, n) in enumerate(shapes)]
+    M, X, Q = (list(t) for t in zip(*[[t.cuda().contiguous() for t in S.initial_state(v, 0, device="cpu")] for v in w]))
+    streams = [S.GradientStream(v, 0, device="cpu") for v in w]
+    Ls = [cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC) for m, n in shapes]
+    grp = cdl.Group(Ls)
+    for t in range(2):
+        G = [s.next().cuda() for s in streams]
+        _, errs = group_step_and_compare(grp, Ls, G, M, X, Q, 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC)
+        for i, d in errs.items():
+            print(shapes[i], r, t + 1, {k: v for k, v in d.items() if k.startswith("err") or k == "kappa"}, flush=True)
+            check_errors(d, False)
 
 
 def _row_err(a, b):
