@@ -98,22 +98,12 @@ int plan_splits(int M, int N, int K, int nl, bool fp64, int* kchunk, int pieces 
   return (K + kc - 1) / kc;
 }
 
-// K slices of a product on the int8 MFMA: at least two workgroups per CU (one
-// is resident) over the `conc` units whose products run side by side, slices
-// at least 256 deep, and no more of them than the fp64
-// kernel's partials of one layer, so that the same workspace holds them.
-// False when a slice would be longer than exact int32 sums allow.
-bool plan_i8(int M, int N, int K, int nl, int conc, int* splits, int* kchunk) {
+// K slices of a product on the int8 MFMA (plan_i8_slices).
+void plan_i8(int M, int N, int K, int nl, int conc, int* splits, int* kchunk) {
   const int bm = cd::gemm_i8_bm(N), bn = cd::gemm_i8_bn(N);
-  const long long tiles = 1LL * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * nl;
   int kc;
-  const int cap = plan_splits(M, N, K, 1, true, &kc);
-  int s = 1;
-  while (tiles * s * conc < 512 && K / (2 * s) >= 256 && 2 * s <= cap) s *= 2;
-  kc = ((K + s - 1) / s + 63) / 64 * 64;
-  *kchunk = kc;
-  *splits = (K + kc - 1) / kc;
-  return kc <= cd::I8_KMAX;
+  const int most = plan_splits(M, N, K, 1, true, &kc);
+  cd::plan_i8_slices(1LL * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * nl, K, conc, most, cd::I8_KMAX, splits, kchunk);
 }
 
 // ---- optional per-kernel timing (HIP events on the launch stream) ----------
@@ -715,9 +705,9 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
     const int most = plan_splits(r, r, m, 1, true, &kc, 0, true);
     int sp = 1;
     while (tiles * sp < 256 && m / (2 * sp) >= 256 && 2 * sp <= most) sp *= 2;
+    while ((m - 1) / sp + 1 > cd::I8_KMAX) sp *= 2;   // int32 sums stay exact
     ia.kchunk = ((m + sp - 1) / sp + 63) / 64 * 64;
     ia.splits = (m + ia.kchunk - 1) / ia.kchunk;
-    if (ia.kchunk > cd::I8_KMAX) return CD_OK;
     const size_t need = cd::i8_bytes(r, ia.splits, ia.kchunk);
     for (int j = 0; j < nl; ++j)
       if (need > cap(j) || static_cast<size_t>(ia.splits) * r * r > lay(j)->gram_cap) return CD_OK;
@@ -753,8 +743,8 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
   // R = B^T P; each the digit planes of the small operand (K x r, fp32 or
   // fp64), the product and the sum of its K slices.  done = false: they stay on
   // the fp64 MFMA (ranks below I8_RMIN, where that kernel's narrow tiles pad
-  // less and streaming B bounds both; slices too long for int32 sums; planes or
-  // maxima that the workspace has no room for, in either product).
+  // less and streaming B bounds both; planes, maxima or partials that the
+  // workspace has no room for, in either product).
   auto gemm_i8 = [&](bool first, auto Aof, auto Bof, auto Cof, bool* done) -> cd_status {
     *done = false;
     cd::I8Args ia{};
@@ -765,7 +755,7 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
       return CD_OK;
     for (const bool other : {true, false}) {   // the other product's plan, then this one's
       const int Mp = first != other ? m : n, Kp = first != other ? n : m;
-      if (!plan_i8(Mp, r, Kp, nl, conc, &ia.splits, &ia.kchunk)) return CD_OK;
+      plan_i8(Mp, r, Kp, nl, conc, &ia.splits, &ia.kchunk);
       const size_t need = cd::i8_bytes(r, ia.splits, ia.kchunk);
       for (int j = 0; j < nl; ++j)
         if (need > lay(j)->digit_cap || (ia.splits > 1 && sizeof(double) * ia.splits * Mp * r > lay(j)->split_cap))

@@ -42,6 +42,20 @@ inline std::vector<std::vector<int>> plan_stream_batches(const std::vector<long 
   return out;
 }
 
+// K slices of a product of `tiles` workgroups on the int8 MFMA: at least two
+// workgroups per CU (one is resident) over the `conc` units whose products run
+// side by side, slices at least 256 deep, and no more of them than `most`, the
+// fp64 kernel's partials of one layer, so that the same workspace holds them.
+// Slices longer than kmax, the most rows that int32 sums hold exactly, are
+// halved on, grid full or not (the caller sees whether the partials fit).
+inline void plan_i8_slices(long long tiles, int K, int conc, int most, int kmax, int* splits, int* kchunk) {
+  int s = 1;
+  while (tiles * s * conc < 512 && K / (2 * s) >= 256 && 2 * s <= most) s *= 2;
+  while ((K - 1) / s + 1 > kmax) s *= 2;
+  *kchunk = ((K - 1) / s + 1 + 63) / 64 * 64;
+  *splits = (K - 1) / *kchunk + 1;
+}
+
 // How many units' launches a unit's K slices are planned for, where units 0 ..
 // nu-1 of work[u] values each run side by side on nside + 1 streams: all of
 // them, but one where all the others together have less than 1/128 of the

@@ -3,7 +3,8 @@
 // shapes "m n", "<layers> <blocks>" each; "range": the tiles of the pass for
 // row and column maxima for "m n room", "<ok> <tr> <tc> <partials>"; "colnorm":
 // workgroups of the launch that normalises R and cuts P for "n m per most";
-// "conc": units that unit u of the given work is planned for, "nside u work ...".
+// "i8": K slices of an int8 product for "tiles K conc most kmax", "<slices>
+// <rows>"; "conc": units that unit u of the given work is planned for, "nside u work ...".
 // Built by the CPU tests with a plain C++ compiler against the library's
 // planning header (it has no HIP dependency).
 #include <cstdio>
@@ -29,6 +30,15 @@ int main(int argc, char** argv) {
     long long n, m, per, most;
     while (std::scanf("%lld %lld %lld %lld", &n, &m, &per, &most) == 4)
       std::printf("%lld\n", cd::colnorm_blocks(n, m, per, most));
+    return 0;
+  }
+  if (!std::strcmp(mode, "i8")) {
+    long long tiles;
+    int K, conc, most, kmax, splits, kchunk;
+    while (std::scanf("%lld %d %d %d %d", &tiles, &K, &conc, &most, &kmax) == 5) {
+      cd::plan_i8_slices(tiles, K, conc, most, kmax, &splits, &kchunk);
+      std::printf("%d %d\n", splits, kchunk);
+    }
     return 0;
   }
   if (!std::strcmp(mode, "conc")) {

@@ -202,6 +202,21 @@ def test_colnorm_launch_has_work_for_the_taller_of_r_and_p(tmp_path):
     assert _plan(tmp_path, rows, "colnorm") == [(4096,), (4096,), (250,), (1,), (4096,), (4096,)]
 
 
+def test_int8_slices_stay_exact_in_int32(tmp_path):
+    """K slices of an int8 product: whole, of a multiple of 64 rows, never longer
+    than int32 sums hold exactly, also where the grid is full without a split; at
+    most the fp64 kernel's count where the length allows it."""
+    kmax = 16384
+    rows = [(t, K, c, most, kmax) for t in (1, 100, 512, 4096) for K in (33, 256, 511, 512, 4096, 16384, 16385, 32768, 50304, 10 ** 6)
+            for c in (1, 4) for most in (1, 4, 32)]
+    for (t, K, c, most, _), (s, kc) in zip(rows, _plan(tmp_path, rows, "i8")):
+        assert kc % 64 == 0 and kc <= kmax and (s - 1) * kc < K <= s * kc, (t, K, c, most)
+        assert s <= most or s <= 2 * (-(-K // kmax)) and K > kmax, (t, K, c, most)
+        if t * c >= 512 and K <= kmax:
+            assert s == 1
+    assert _plan(tmp_path, [(512, 32768, 1, 1, kmax), (512, 32768, 1, 4, kmax)], "i8") == [(2, 16384)] * 2
+
+
 def test_slices_are_planned_for_the_units_that_share_the_chip(tmp_path):
     """A unit's K slices are planned for all units side by side, unless the
     others together have less than 1/128 of its work; a unit alone for itself,

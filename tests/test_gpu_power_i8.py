@@ -234,6 +234,21 @@ def test_long_slices():
     assert all(torch.isfinite(M[i]).all() and torch.isfinite(Q[i]).all() for i in range(layers) if i != sick)
 
 
+# a grid that is full without a split, and K past the 16384 rows that int32 sums
+# hold exactly: two slices all the same
+def test_slices_past_the_exact_sums():
+    m, n, r, layers = 2048, 16450, 512, 4
+    g = torch.Generator("cuda").manual_seed(840)
+    randn = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+    G = [randn(m, 24) @ randn(24, n) + 0.1 * randn(m, n) for _ in range(layers)]
+    M, X = ([0.02 * randn(m, n) for _ in range(layers)] for _ in range(2))
+    Q = [torch.linalg.qr(randn(n, r))[0].contiguous() for _ in range(layers)]
+    Ls = [cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC) for _ in range(layers)]
+    _, errs = group_step_and_compare(cdl.Group(Ls), Ls, G, M, X, Q, 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC, check=[3])
+    print({k: v for k, v in errs[3].items() if k.startswith("err") or k == "kappa"}, flush=True)
+    check_errors(errs[3], False)
+
+
 # blocks with a NaN or an Inf are formed again on the fp64 MFMA, not entry by
 # entry: at 4096 x 16384, r = 1024 a step with a NaN takes 1.55 times one
 # without (entry by entry 3.1, 16.4 ms of 5.3)
