@@ -264,7 +264,8 @@ cd_status cd_group_kernel_times(cd_group* group, cd_kernel_time* out, int max_ki
  * comma-separated list of the names cd_group_kernel_times() reports (NULL or
  * "" = every kind, the default).  The events cost several microseconds of
  * idle time at each bracketed launch, so a measurement of whole steps
- * brackets only the kernel it reports.  Applies from the next step; the
+ * brackets only the kernel it reports.  The names of kernels that others have
+ * replaced (trsm_f64, trtri_f64, gram_i8x21) bracket those.  Applies from the next step; the
  * setting survives cd_group_set_timing().  CD_EINVAL for an unknown name
  * (the previous setting is then kept). */
 cd_status cd_group_set_timing_kinds(cd_group* group, const char* kinds);

@@ -119,6 +119,9 @@ const char* const kKindName[K_NKINDS] = {
     "slice_i8", "power_bq_i8x21", "power_btp_i8x21", "update_f16x3", "gram_i8x26",
     "range_i8"};
 static_assert(K_NKINDS <= 32, "the timing mask holds one bit per kind");
+// Names of kernels that others have replaced, still accepted where a kind is named.
+const struct { const char* name; int kind; } kRetired[] = {
+    {"trsm_f64", K_APPLY_F64}, {"trtri_f64", K_CHOL}, {"gram_i8x21", K_GRAM_I8}};
 
 // Timing events only measure: recording them without the system-scope fence
 // (cache write-back and invalidate) keeps them from stretching the gaps
@@ -1737,6 +1740,8 @@ cd_status cd_group_set_timing_kinds(cd_group* group, const char* kinds) {
     const std::string name = list.substr(b, e - b);
     int k = 0;
     while (k < K_NKINDS && name != kKindName[k]) ++k;
+    for (const auto& old : kRetired)
+      if (name == old.name) k = old.kind;
     if (k == K_NKINDS) return fail(CD_EINVAL, "unknown kernel kind '%s'", name.c_str());
     mask |= 1u << k;
     b = e + 1;

@@ -696,6 +696,22 @@ def test_kernel_timing_brackets_only_the_named_kinds():
         assert np.array_equal(a, b)
 
 
+def test_retired_kernel_names_are_still_accepted():
+    """The names of kernels that others have replaced restrict the timing to
+    those others: the triangular solve and inverse of the fp32 path to the
+    apply and the factorisation that took their place."""
+    m, n, r = 384, 512, 96
+    w = S.small_workload(m, n, r)
+    L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+    Gp = cdl.Group([L])
+    M, X, Q = _state(w, 0)
+    Gp.set_timing(True, ["trsm_f64", "trtri_f64", "gram_i8x21"])
+    Gp.step([S.GradientStream(w, 0, device="cpu").next().to(DEV)], [M], [X], [Q], w.mu, w.eta, r)
+    kt = Gp.kernel_times()
+    Gp.set_timing(False)
+    assert set(kt) - {"gram_i8x26"} == {"apply_f64", "cholesky_f64"}
+
+
 def test_full_timing_runs_batches_serially_with_identical_results():
     """With every kernel kind timed, the shape batches of the sync branch run
     one after another on the caller's stream; the results are bit-identical
