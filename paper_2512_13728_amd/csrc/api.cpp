@@ -74,8 +74,8 @@ struct DeviceGuard {
 // K-splitting so that the launches of the `conc` units that run side by side
 // have >= ~1024 working blocks together, each slice >= 256 deep.  (Slices for
 // 1024 blocks per unit: one 2048-wide transformer block, four units, wrote and
-// added 16 partials per product, 1.66 ms a sync step; now 4 to 8, 1.53.  The
-// Gram matrices keep the larger count, their partials are small: the 160M set
+// added 16 partials per product, 1.66 ms a sync step; with 4 to 8 of them but for
+// P~ 1.58.  The Gram matrices keep the larger count, their partials are small: the 160M set
 // 2.18 ms against 2.20.)  pieces > 0 selects the tile shape of the bf16-split kernels, else
 // the fp32 / fp64 MFMA kernels; `upper` counts only the tiles an upper-only
 // product computes (the others exit at once).
@@ -653,7 +653,12 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
       ga.splits = 1;
       ga.kchunk = (K + cd::GBK - 1) / cd::GBK * cd::GBK;
     } else {
-      ga.splits = plan_splits(Mr, Nr, K, nl, acc64, &ga.kchunk, pieces, upper, acc64 ? 1 : conc);
+      // P~ keeps the slices of a unit alone: the rounding of its fp32 sums,
+      // longer with fewer slices, comes out times kappa(P~) (one 2048-wide
+      // block, second sync step: Q 1.212e-3 from float64 planned for four
+      // units, 1.193e-3 for one; the sync step 1.50 and 1.58 ms, the 160M
+      // set's with bf16 gradients 1.19 and 1.18)
+      ga.splits = plan_splits(Mr, Nr, K, nl, acc64, &ga.kchunk, pieces, upper, acc64 || stage == 0 ? 1 : conc);
     }
     ga.split_stride = 1LL * Mr * Nr;
     if (ga.splits > 1) {
