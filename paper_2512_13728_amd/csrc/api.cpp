@@ -700,12 +700,13 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
   auto part = [&](int j) { return lay(j)->split_part; };
   // The Gram matrix of an fp64 panel (P~, then P1) of fp32-gradient layers on
   // the int8 MFMA, its digit planes in `room` (bytes `cap`), which the panel
-  // does not use.  done = false: it stays on the fp64 MFMA (see I8_GRAM_ALWAYS;
+  // does not use.  done = false: it stays on the fp64 MFMA (see I8_GRAM_RMIN;
   // or no room).
   auto gram_i8 = [&](auto Pof, auto room, auto cap, bool* done) -> cd_status {
     *done = false;
     cd::I8Args ia{};
-    if (r < cd::I8_GRAM_ALWAYS && (r < cd::I8_GRAM_RMIN || conc == 1 || m >= cd::I8_GRAM_ROWS)) return CD_OK;
+    const bool takes = conc == 1 ? 1.0 * m * r * r * nl >= cd::I8_ALONE_MIN : r >= cd::I8_GRAM_WIDE || m < cd::I8_GRAM_ROWS;
+    if (r < cd::I8_GRAM_RMIN || !takes) return CD_OK;
     long long tiles = 0;   // 128 x 64, not wholly below the diagonal
     for (int i = 0; i < r; i += 128) tiles += (r - i + 63) / 64;
     tiles *= nl;
@@ -750,16 +751,17 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
   // (`first`; before it B's row and column maxima, the scales of both), then
   // R = B^T P; each the digit planes of the small operand (K x r, fp32 or
   // fp64), the product and the sum of its K slices.  done = false: they stay on
-  // the fp64 MFMA (ranks below I8_RMIN, where that kernel's narrow tiles pad
-  // less and streaming B bounds both; planes, maxima or partials that the
-  // workspace has no room for, in either product).
+  // the fp64 MFMA (narrow or small, see I8_RMIN and I8_ALONE_MIN; planes, maxima
+  // or partials that the workspace has no room for, in either product).
   auto gemm_i8 = [&](bool first, auto Aof, auto Bof, auto Cof, bool* done) -> cd_status {
     *done = false;
     cd::I8Args ia{};
     cd::RangeArgs ra8{};
     size_t room = ~static_cast<size_t>(0) >> 1;
     for (int j = 0; j < nl; ++j) room = std::min(room, lay(j)->split_cap);
-    if (r < cd::I8_RMIN || !cd::plan_range(m, n, static_cast<long long>(room / sizeof(float)), &ra8.tr, &ra8.tc))
+    const double mults = 1.0 * m * n * nl * ((r + 63) / 64 * 64);
+    if (r < cd::I8_RMIN || (conc == 1 && mults < cd::I8_ALONE_MIN) ||
+        !cd::plan_range(m, n, static_cast<long long>(room / sizeof(float)), &ra8.tr, &ra8.tc))
       return CD_OK;
     for (const bool other : {true, false}) {   // the other product's plan, then this one's
       const int Mp = first != other ? m : n, Kp = first != other ? n : m;

@@ -152,21 +152,34 @@ inline bool gemm_acc64(GemmKind k) { return k != GemmKind::F32; }
 // when a_kc, else A[k*lda + i]) and B K x N row-major, fp32 or fp64, cut into
 // digit planes by launch_slice8 first.  K is split in `splits` slices of
 // kchunk (a multiple of 64, at most I8_KMAX: the int32 sums stay exact).
-constexpr int I8_RMIN = 33;        // narrower products stay on the fp64 MFMA kernel
-// Gram matrices take it at I8_GRAM_ALWAYS columns and more, where multiplying
-// bounds them (fp64 MFMA / int8 sync steps: 1024 x 1024, r = 512, 8 layers 1098 /
-// 1032 us, 16 layers 1777 / 1624; two 2048-wide blocks, r = 512, 4497 / 4280; r =
-// 384 0.98 to 1.04 times), and from I8_GRAM_RMIN to there only where units run
-// side by side and the panel has fewer than I8_GRAM_ROWS rows: the fp64 kernel
-// then has two slices at most, and its long workgroups fill the other units'
-// CUs (odd shapes of two layers each, r = 130, 559 / 541; of eight, 1183 / 1147;
-// 768-wide sets of 1 to 12 blocks, r = 96 and 192: 0.5 to 3% ahead of fp64).
-// Elsewhere the fp64 kernel is level or ahead, as the digits are a launch and a
-// pass of their own: 1024 x 1024, r = 128, one layer 262 / 265, 16 layers 497 /
-// 532; 2048-wide blocks, r = 128, 859 / 882; 768 x 768, r = 128, 32 layers 628 /
-// 653; 1024 x 1024 and 2048 x 1024, r = 128, eight of each 667 / 724.
+// The power products take it above 32 columns (the fp64 kernel's narrow tiles pad
+// less below, and streaming B bounds both), and for a unit that runs alone from
+// this many multiplications on, m n r with r rounded up to 64 and all its
+// layers together.  Below, the pass over B for the scales and the launches of the
+// digits cost more than the products save; fp64 / int8 sync steps in us: 1024 x
+// 1024, r = 64 (0.07e9) 178 / 188, four of them at r = 192 (0.8e9) 373 / 388; 2048
+// x 2048, r = 64 (0.3e9) 200 / 216, r = 256 (1.07e9) 441 / 443, r = 384 (1.6e9) 625
+// / 606; two of them at r = 128 (1.07e9) 360 / 368, at r = 192 (1.6e9) 473 / 461;
+// 4096 x 4096, r = 64 (1.07e9) 323 / 337, r = 128 (2.1e9) 480 / 457.  Units side by
+// side fill the chip at any size: 1024 x 1024 with 1024 x 1000, r = 64, 242 / 238, r
+// = 256, 452 / 434; four odd shapes of two layers, r = 48, 388 / 372.
+constexpr int I8_RMIN = 33;
+constexpr double I8_ALONE_MIN = 1.3e9;
+// Gram matrices of a unit that runs alone take it from the same number of
+// multiplications on, m r^2 over its layers: fp64 / int8 sync steps of 1024 x
+// 1024, r = 128, 16 layers (0.3e9) 497 / 532, r = 256 (1.07e9) 787 / 795, r = 320
+// (1.7e9) 1056 / 1005, r = 512 (4.3e9) 1777 / 1624; 4096 x 4096, r = 512 (1.07e9) 1111
+// / 1103; 50304 x 768, r = 192 (1.9e9) 1347 / 1258.  Units side by side take it
+// from I8_GRAM_WIDE columns on (two 2048-wide blocks, r = 512, 4497 / 4280; 768-wide
+// blocks, r = 384, 1568 / 1520), and from I8_GRAM_RMIN on where the panel has fewer
+// than I8_GRAM_ROWS rows: the fp64 kernel then has two slices at most, and its
+// long workgroups fill the other units' CUs (odd shapes of two layers each, r =
+// 130, 559 / 541; of eight, 1183 / 1147; 768-wide sets of 1 to 12 blocks, r = 96 and
+// 192: 0.5 to 3% ahead of fp64).  Elsewhere the fp64 kernel is level or ahead, as
+// the digits are a launch and a pass of their own: 2048-wide blocks, r = 128, 859 /
+// 882; 1024 x 1024 and 2048 x 1024, r = 128, eight of each, 667 / 724.
 constexpr int I8_GRAM_RMIN = 65;
-constexpr int I8_GRAM_ALWAYS = 384;
+constexpr int I8_GRAM_WIDE = 384;
 constexpr int I8_GRAM_ROWS = 1024;
 struct I8Args {
   int M, N, K, lda;

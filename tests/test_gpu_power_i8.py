@@ -1,6 +1,5 @@
 """The int8-MFMA power products of fp32-gradient layers (k_gemm_i8.hip) at the
-edges of their tiles, stages, K slices and digit planes: sync steps of one
-layer against the float64 oracle, teacher-forced, within the bounds of
+edges of their tiles, stages, K slices and digit planes: sync steps against the float64 oracle, teacher-forced, within the bounds of
 gpu_util.check_errors (fp64-accurate products behind fp32 state)."""
 import os
 import sys
@@ -20,6 +19,25 @@ from gpu_util import (buffer_f32, check_errors, device_to_numpy, f32, f64, group
 pytestmark = pytest.mark.gpu
 
 
+class Beside:
+    """A layer that steps in one group with a layer of another shape: units side
+    by side take the digits at any size, where a small layer alone stays on the
+    fp64 MFMA.  Steps and answers as the layer itself."""
+
+    def __init__(self, m, n, r, **kw):
+        self.layers = [cdl.Layer(m, n, r, **kw), cdl.Layer(m, n + 4, r, **kw)]
+        self.group = cdl.Group(self.layers)
+        g = torch.Generator("cuda").manual_seed(1)
+        self.other = [torch.randn(*s, device="cuda", generator=g) for s in [(m, n + 4)] * 3 + [(n + 4, r)]]
+
+    def step(self, G, M, X, Q, mu, eta, r):
+        _, flag, per, status = self.group.step(*([a, b] for a, b in zip((G, M, X, Q), self.other)), mu, eta, r)
+        return per[0], flag, status
+
+    def __getattr__(self, name):
+        return getattr(self.layers[0], name)
+
+
 # the narrowest rank of the path and the one below it; column blocks of 32,
 # tiles of 64 and 128 columns whole and partial; K of one stage and one past
 # it, several slices, slices with a partial last chunk; rows not a multiple of
@@ -35,7 +53,7 @@ pytestmark = pytest.mark.gpu
 def test_power_product_edges(m, n, r):
     w = S.small_workload(m, n, r, k=min(24, r - 1), stream_id=700 + r)
     M, X, Q = (t.cuda().contiguous() for t in S.initial_state(w, 0, device="cpu"))
-    L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+    L = Beside(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
     stream = S.GradientStream(w, 0, device="cpu")
     for t in range(2):
         d = step_and_compare(L, stream.next().cuda(), M, X, Q, 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC)
@@ -60,7 +78,7 @@ def test_power_product_scales(kind):
     else:
         # a range of 2^12: kappa(P~) stays below the 3e6 at which pivots are floored
         Q *= torch.logspace(-6, 6, r, base=2.0, device="cuda")[None, :]
-    L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+    L = Beside(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
     d = step_and_compare(L, G, M, X, Q.contiguous(), 0.95, 0.01, r, 0.5, O.POLICY_ALWAYS_SYNC)
     print(kind, {k: v for k, v in d.items() if k.startswith("err") or k == "kappa"}, flush=True)
     check_errors(d, False)
@@ -77,7 +95,7 @@ def test_power_product_nonfinite(m, n, r, bad):
     M, X, Q = (t.cuda().contiguous() for t in S.initial_state(w, 0, device="cpu"))
     G = S.GradientStream(w, 0, device="cpu").next().cuda()
     G[7, 11] = bad
-    L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+    L = Beside(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
     _, flag, status = L.step(G, M, X, Q, 0.95, 0.01, r)
     torch.cuda.synchronize()
     assert flag and status != 0
@@ -125,10 +143,9 @@ def _dominant(m, n, r, f, seed):
 
 
 # the smallest pivots of the digit Gram matrix are 5 to 80 times the floor of 1e-13
-# of its largest diagonal entry (kappa(P~) up to 6e6), in K slices of 256 (one
-# layer), 450 and 500 (units side by side) and of all 2050 rows (13 layers fill the
-# chip)
-@pytest.mark.parametrize("shapes,r,f", [([(2048, 512)], 400, 1e5), ([(1000, 1024), (900, 1024)], 96, 2e5), ([(2050, 770)] * 13, 512, 6e4)])
+# of its largest diagonal entry (kappa(P~) up to 6e6), in K slices of 256, 450 and
+# 500 (units side by side) and of all 2050 rows (13 layers fill the chip)
+@pytest.mark.parametrize("shapes,r,f", [([(2048, 512), (2048, 516)], 400, 1e5), ([(1000, 1024), (900, 1024)], 96, 2e5), ([(2050, 770)] * 13, 512, 6e4)])
 def test_gram_dominant_row(shapes, r, f):
     Ls = [cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC) for m, n in shapes]
     G, M, X, Q = (list(t) for t in zip(*[_dominant(m, n, r, f, 791 + i) for i, (m, n) in enumerate(shapes)]))
@@ -143,11 +160,10 @@ def test_gram_dominant_row(shapes, r, f):
 
 
 # digit Gram matrices at the edges of their 64- and 128-column tiles and 32-column
-# blocks: below 384 columns where two units run side by side, from there on alone;
-# ragged K slices
+# blocks, in two units side by side; ragged K slices
 @pytest.mark.parametrize("r", [64, 65, 96, 97, 128, 129, 192, 193, 383, 384, 417, 513])
 def test_gram_edges(r):
-    shapes = [(701, 600), (650, 731)] if r < 384 else [(701, 600)]
+    shapes = [(701, 600), (650, 731)]
     w = [S.small_workload(m, n, r, k=24, stream_id=870 + r + i) for i, (m, n) in enumerate(shapes)]
     M, X, Q = (list(t) for t in zip(*[[t.cuda().contiguous() for t in S.initial_state(v, 0, device="cpu")] for v in w]))
     streams = [S.GradientStream(v, 0, device="cpu") for v in w]
@@ -185,7 +201,7 @@ def test_small_rows_and_columns(m, n, kind, r):
     M = torch.zeros_like(G)
     X.zero_()
     B, Q0 = f64(G), f64(Q)
-    L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+    L = Beside(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
     L.step(G, M, X, Q, 0.95, 0.01, r)
     torch.cuda.synchronize()
     Pa, Ra = L.last_factors()
@@ -274,3 +290,24 @@ def test_nonfinite_step_time():
             times[bad] = min(times.get(bad, 1e9), a.elapsed_time(b))
     print(times, flush=True)
     assert times[True] < 2.2 * times[False], times
+
+
+# where a layer alone goes from the fp64 MFMA to the digits: 1.3e9 multiplications,
+# m n times r rounded up to 64
+@pytest.mark.parametrize("r,digits", [(256, False), (320, True)])
+def test_small_layers_alone_stay_on_fp64(r, digits):
+    m = n = 2048
+    w = S.small_workload(m, n, r, k=24, stream_id=890)
+    M, X, Q = (t.cuda().contiguous() for t in S.initial_state(w, 0, device="cpu"))
+    L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+    grp = cdl.Group([L])
+    grp.set_timing(True)
+    _, errs = group_step_and_compare(grp, [L], [S.GradientStream(w, 0, device="cpu").next().cuda()], [M], [X], [Q], 0.95, 0.01,
+                                     r, 0.5, O.POLICY_ALWAYS_SYNC)
+    kinds = set(grp.kernel_times())
+    grp.set_timing(False)
+    check_errors(errs[0], False)
+    assert ("power_bq_i8x21" in kinds) == ("power_btp_i8x21" in kinds) == digits, kinds
+    assert ("power_bq_f64" in kinds) == ("power_btp_f64" in kinds) != digits, kinds
+    # the Gram matrices, m r^2, are far from it at either rank
+    assert "gram_f64" in kinds and "gram_i8x26" not in kinds
