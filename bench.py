@@ -62,7 +62,7 @@ KIND_BOUND = {
     "reduce_splits": ("hbm", None, 1), "colnorm": ("hbm", None, 1),
     "power_bq_f64": ("mfma", "f64", 1), "gram_f64": ("mfma", "f64", 1), "apply_f64": ("mfma", "f64", 1),
     "power_btp_f64": ("mfma", "f64", 1),
-    # fp64-accurate products from 21 digit products on the int8 MFMA
+    # products of 47-bit operands from 21 digit products on the int8 MFMA (Gram matrices 26)
     "power_bq_i8x21": ("mfma", "i8", 21), "power_btp_i8x21": ("mfma", "i8", 21), "slice_i8": ("hbm", None, 1),
     "gram_i8x26": ("mfma", "i8", 26), "range_i8": ("hbm", None, 1),
     "cholesky_f64": ("mfma", "f64", 1), "power_bq_bf16x6": ("mfma", "bf16", 6),
@@ -714,7 +714,7 @@ def main():
         "vs_baseline": None,
         # the contractions of bf16-gradient layers run on the bf16 MFMA (split
         # fp32 operands for the power iteration, plain bf16 for the rank-r
-        # update); fp32-gradient layers compute in fp32 and fp64
+        # update); fp32-gradient layers compute to fp32 and fp64 accuracy
         "dtype": "bf16" if w.grad_dtype == "bf16" else "f32",
         "data": "synthetic",
         "config": {
@@ -727,8 +727,10 @@ def main():
                                       "accumulation (3 bf16 slices per value, 9 products on bf16 MFMA) and "
                                       "Cholesky in fp64, pass 1 fp32-accurate (bf16 x 6); M/X update bf16 "
                                       "products, fp32 accumulation" if w.grad_dtype == "bf16" else
-                                      "P~ = BQ, R = B^T P, Gram and CholQR in fp64; the M/X update on bf16 "
-                                      "MFMA with 3-piece fp32 splits (fp32 vector units at r <= 32)"),
+                                      "P~ = BQ, R = B^T P and Gram on the fp64 MFMA or in 47-bit digits on the "
+                                      "int8 MFMA (21 products, Gram 26), CholQR in fp64; the M/X update "
+                                      "fp32-accurate: fp32 vector units at r <= 32, 3 bf16 pieces to r = 128, "
+                                      "2 scaled fp16 pieces above"),
             "policy": args.policy + (f" (H = {args.H})" if args.policy == "every_h" else ""),
             "steps_mode": "asynchronous (no host read per step)" if asyn else "blocking (gate read per step)",
             "tau": w.tau, "trajectory_steps": K,
