@@ -869,10 +869,10 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
   // bf16-gradient layers: the power-iteration products P~ = B Q and R = B^T P
   // use two-piece splits (three bf16 products, relative error about 2^-16,
   // an order below what the plain-bf16 rank-r update of M contributes);
-  // fp32 layers keep both to fp64 accuracy (gemm_i8, fp64 at r <= 32).
+  // fp32 layers form both in 47-bit digits (gemm_i8) or on the fp64 MFMA.
   const bool fast = g->g_bf16;
   if (stage == 0) {
-    // P~ = B Q (B lives in M): to fp64 for fp32 layers, into pa; bf16 x 3 for
+    // P~ = B Q (B lives in M): fp64 for fp32 layers, into pa; bf16 x 3 for
     // bf16-gradient layers, into the fp32 panel P
     if (fast)
       return gemm(K_PBQ_BF, 2.0 * mn * r, 4.0 * mn + 4.0 * nr + 4.0 * mr, cd::GemmKind::F32, m, r, n,
@@ -967,7 +967,7 @@ cd_status enqueue_sync(cd_group* g, const Unit& unit, const void* const* G, int 
                 r, false, In, In, [&](int j) { return static_cast<void*>(lay(j)->W); }, part, 3, true);
   }
   // R = B^T P: bf16-gradient layers from the fp32 P with two-piece splits;
-  // fp32 layers from the fp64 P to fp64 accuracy (R_j = B^T P_j cancels for
+  // fp32 layers from the fp64 P, in digits or fp64 (R_j = B^T P_j cancels for
   // the weak directions, by up to ||B||_2 / ||R_j||, which fp32 products and
   // sums would pass on to Q)
   auto Bf = [&](int j) { return static_cast<const void*>(M[sel[j]]); };

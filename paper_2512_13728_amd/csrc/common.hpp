@@ -147,7 +147,7 @@ int gemm_bm(int N, bool fp64);     // tile rows the launcher uses for this N
 int gemm_bn(int N, bool fp64);     // tile columns
 inline bool gemm_acc64(GemmKind k) { return k != GemmKind::F32; }
 
-// ---- fp64-accurate products on the int8 MFMA (k_gemm_i8.hip) ----------------
+// ---- products in 47-bit digits on the int8 MFMA (k_gemm_i8.hip) --------------
 // C[M x N] = A[M x K] B[K x N] with A = an fp32 matrix (A(i,k) at A[i*lda + k]
 // when a_kc, else A[k*lda + i]) and B K x N row-major, fp32 or fp64, cut into
 // digit planes by launch_slice8 first.  K is split in `splits` slices of

@@ -63,7 +63,7 @@ def test_power_product_edges(m, n, r):
 
 # the digits are relative to the largest |B| and to each column's largest |Q|:
 # magnitudes near both ends of fp32, and a few entries far above the others
-@pytest.mark.parametrize("kind", ["large", "small", "outlier", "column scales"])
+@pytest.mark.parametrize("kind", ["large", "small", "outlier", "spike", "column scales"])
 def test_power_product_scales(kind):
     m, n, r = 192, 320, 48
     w = S.small_workload(m, n, r, k=24, stream_id=760)
@@ -72,8 +72,8 @@ def test_power_product_scales(kind):
     if kind in ("large", "small"):
         f = 2.0 ** (60 if kind == "large" else -60)
         M, G = M * f, G * f
-    elif kind == "outlier":
-        G[3, 5] += 1e3
+    elif kind in ("outlier", "spike"):
+        G[3, 5] += 1e3 if kind == "outlier" else 1e5
         G[100, 200] -= 1e3
     else:
         # a range of 2^12: kappa(P~) stays below the 3e6 at which pivots are floored
@@ -311,3 +311,50 @@ def test_small_layers_alone_stay_on_fp64(r, digits):
     assert ("power_bq_f64" in kinds) == ("power_btp_f64" in kinds) != digits, kinds
     # the Gram matrices, m r^2, are far from it at either rank
     assert "gram_f64" in kinds and "gram_i8x26" not in kinds
+
+
+# the allocation-free step carves the digits, the maxima and the partials from its
+# fixed array: bit-identical to the layer's own step, above and below the size from
+# which a layer alone takes the digits, after each other in the same array
+def test_static_step_takes_the_same_products():
+    for m, n, r in [(4096, 16384, 64), (700, 901, 97), (4096, 16384, 64)]:
+        g = torch.Generator("cuda").manual_seed(860 + r)
+        randn = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+        a = [0.02 * randn(m, n), 0.02 * randn(m, n), torch.linalg.qr(randn(n, r))[0].contiguous()]
+        b = [t.clone() for t in a]
+        L = cdl.Layer(m, n, r, policy=cdl.POLICY_ALWAYS_SYNC)
+        prev, step = torch.zeros(1, dtype=torch.float64, device="cuda"), 0
+        for _ in range(2):
+            G = randn(m, 16) @ randn(16, n) + 0.1 * randn(m, n)
+            one = L.step(G, *a, 0.95, 0.01, r)
+            rm, flag, status, step = cdl.step_static(m, n, r, prev, step, G, *b, 0.95, 0.01, r, policy=cdl.POLICY_ALWAYS_SYNC)
+            torch.cuda.synchronize()
+            assert one == (rm, flag, status)
+            assert all(torch.equal(x, y) for x, y in zip(a, b)), (m, n, r, step)
+
+
+# asynchronous steps enqueue both branches on the gate's decision: the digit
+# products, their maxima and the fp16 pieces run on the steps that sync and
+# leave everything alone on those that do not
+@pytest.mark.parametrize("r", [48, 160])
+def test_async_steps_bit_identical_to_blocking(r):
+    shapes, steps, spikes = [(256, 384), (384, 257), (256, 384)], 8, (4, 6)
+    g = torch.Generator("cuda").manual_seed(880 + r)
+    randn = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+    G = [[(40.0 if t in spikes else 1.0) * (randn(m, 24) @ randn(24, n) + 0.1 * randn(m, n)) for m, n in shapes] for t in range(steps)]
+    start = [[0.02 * randn(m, n) for m, n in shapes], [0.02 * randn(m, n) for m, n in shapes],
+             [torch.linalg.qr(randn(n, r))[0].contiguous() for _, n in shapes]]
+    runs = []
+    for wait in (True, False):
+        Ls = [cdl.Layer(m, n, r, tau=0.5, weight_decay=0.05) for m, n in shapes]
+        grp = cdl.Group(Ls)
+        state = [[t.clone() for t in v] for v in start]
+        flags = []
+        for t in range(steps):
+            got = grp.step(G[t], *state, 0.95, 0.01, r, wait=wait)
+            flags.append((got if wait else grp.last_result())[1])
+        torch.cuda.synchronize()
+        runs.append((flags, state))
+    assert runs[0][0] == runs[1][0] and runs[0][0][0] and True in runs[0][0][1:] and False in runs[0][0]
+    for a, b in zip(*(sum(s, []) for _, s in runs)):
+        assert torch.equal(a, b)
