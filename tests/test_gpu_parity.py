@@ -276,12 +276,11 @@ def test_rank_deficient_buffer_is_completed(gd, m, n, r, k):
 def test_second_pass_paths_mixed_in_one_launch(m, n, r):
     """Three fp32 layers of one shape step together (one batch, one launch
     per kernel); the middle one's buffer has exact rank 5.  Its pass-0 pivots
-    fall under the floor and the completed columns leave P1^T P1 far from the
-    identity, so its second CholQR pass takes the blocked factorisation, while
-    the other two layers' second pass takes the near-identity factor (their
-    Gram matrices are within 2^-10 of I): both paths in the same launches,
-    gated per layer, at r = 96 (two whole blocks) and r = 160 (a partial third
-    block).  The full-rank layers match the oracle to the fp32 bounds; the
+    fall under the floor, its dead columns are completed and P1^T P1 is far from
+    the identity, while the other two layers' second Gram matrices are within
+    2^-10 of it: the floored and the full-rank factorisation in the same
+    launches, at r = 96 (a partial second block) and r = 160 (a partial third).
+    The full-rank layers match the oracle to the fp32 bounds; the
     deficient one has orthonormal P whose unique columns (and those of R and
     Q, and M = mu B) match the oracle, as test_rank_deficient_buffer_is_completed
     checks for one layer alone."""
